@@ -125,12 +125,32 @@ __device__ inline uint32_t quad_lane(uint32_t v) {
     return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), B * 0x55, 0xf, 0xf, false));
 }
 
-// Decode operands prepared from a piece.
+// Decode operands prepared from a piece.  The e2m1 converter turns a byte's
+// two nibbles into a pair of values, and the gathered codes of a vector lie in
+// one byte as four 2-bit fields; so the operand order of the components is 0,
+// 2, 1, 3 throughout (codes and A alike).
 struct DecOps {
-    uint32_t p01[2], p23[2];  // byte n of word h: nibbles (q_0, q_1) / (q_2, q_3) of vector 4(4h+n)+j
-    f16x4 arow;               // A[j][0..3]
-    f32x4 bvec;               // B[0..3]
+    uint32_t e[2], o[2];  // byte n of word h: nibbles (q_0, q_2) / (q_1, q_3) of vector 4(4h+n)+j
+    f16x4 arow;           // A[j][0, 2, 1, 3]
+    f32x4 bvec;           // B[0..3]
 };
+
+// Per-lane constants of the gathers (j = lane % 4).
+struct DecLane {
+    uint32_t rot4, keep4, rot2, keep2;  // code transpose: rotations and kept fields of its two stages
+    f16x4 unit;                         // 1 at element j
+};
+
+__device__ inline DecLane make_dec_lane(int j) {
+    DecLane l;
+    l.rot4 = j < 2 ? 28u : 4u;
+    l.keep4 = j < 2 ? 0x0f0f0f0fu : 0xf0f0f0f0u;
+    l.rot2 = (j & 1) == 0 ? 30u : 2u;
+    l.keep2 = (j & 1) == 0 ? 0x33333333u : 0xccccccccu;
+    const _Float16 one = static_cast<_Float16>(1.0f), zero = static_cast<_Float16>(0.0f);
+    l.unit = f16x4{j == 0 ? one : zero, j == 1 ? one : zero, j == 2 ? one : zero, j == 3 ? one : zero};
+    return l;
+}
 
 // Lane permutation within each quad (DPP quad_perm): dest lane i reads lane
 // ((CTRL >> 2i) & 3).
@@ -139,62 +159,71 @@ __device__ inline uint32_t quad_perm(uint32_t v) {
     return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xf, 0xf, false));
 }
 
+// bitwise a ? b : c as a truth table of v_bitop3_b32
+constexpr int kSelect = 0xca;
+
+// 4 x 4 transpose of 2-bit fields between the lanes of a quad and the four
+// fields of every byte: lane b's field j goes to lane j's field b.  Two stages
+// of three instructions (exchange, rotate, merge).
+__device__ inline uint32_t transpose_fields(uint32_t w, const DecLane& l) {
+    uint32_t t = quad_perm<0x4e>(w);  // lane ^ 2
+    t = __builtin_amdgcn_alignbit(t, t, l.rot4);
+    w = __builtin_amdgcn_bitop3_b32(l.keep4, w, t, kSelect);
+    t = quad_perm<0xb1>(w);  // lane ^ 1
+    t = __builtin_amdgcn_alignbit(t, t, l.rot2);
+    return __builtin_amdgcn_bitop3_b32(l.keep2, w, t, kSelect);
+}
+
 // Gather, for group 2p + jj, the codes of vectors 4n+j, row j of A and all
 // of B from the four slots of the quad.
 //   Codes: lane b's word holds component b's 2-bit codes, field k of each
-//   byte for vector 4(byte) + k; lane j needs field j of every lane's word,
-//   as nibbles for the e2m1 converter: component 0 in the low nibble, 1 in
-//   the high one (p01), likewise 2 and 3 (p23).  The high nibble comes from a
-//   rotation of the other word by 2j - 4, which lands field j at bits 4-5 of
-//   each byte (bits that wrap around fall outside the mask).
-//   A: lane b holds column b (rows 0, 1 in word al, rows 2, 3 in ah); lane j
-//   needs row j.  A 4 x 4 transpose of 16-bit elements in two butterfly
-//   stages: the word pair across lanes j ^ 2, then the halves across j ^ 1.
-//   B: the word holds B[b] of both groups; each lane needs all four.
+//   byte for vector 4(byte) + k; lane j needs field j of every lane's word:
+//   the transpose above, then two masks.
+//   A: lane b holds column b, lane j needs row j: one 4x4x4 instruction with
+//   the unit matrix (block = row: D[i][n] = sum_k A[k][i] I[k][n], lane n gets
+//   A[n][0..3]), exact in fp32 and exact back in fp16.
+//   B: lane b holds B[b], each lane needs all four: the same with the unit
+//   vector of k = 0.
+// 21 vector instructions and two 4x4x4 for a tile; gathering codes, A and B
+// lane by lane took 40, of the 84 issue slots that bound the kernels that
+// decode (7B layer, 16 tokens: 50.4 -> 48.2 us; prefill at 2048 tokens: 999 ->
+// 967 us).
 // CODES_ONLY (the Eq. 9 fold, where A and B act on the activations): the
 // codes alone.
 template <bool CODES_ONLY = false>
-__device__ inline void prepare(const Piece& pc, int j, int jj, DecOps& d) {
-    const uint32_t cl = jj ? pc.c.z : pc.c.x, ch = jj ? pc.c.w : pc.c.y;
-    const uint32_t al = jj ? pc.a.z : pc.a.x, ah = jj ? pc.a.w : pc.a.y;
-    const uint32_t cw[2][4] = {{quad_lane<0>(cl), quad_lane<1>(cl), quad_lane<2>(cl), quad_lane<3>(cl)},
-                               {quad_lane<0>(ch), quad_lane<1>(ch), quad_lane<2>(ch), quad_lane<3>(ch)}};
-    const int sh = 2 * j;
-    const int rot = (sh - 4) & 31;
+__device__ inline void prepare(const Piece& pc, const DecLane& l, int jj, DecOps& d) {
+    const uint32_t cw[2] = {transpose_fields(jj ? pc.c.z : pc.c.x, l), transpose_fields(jj ? pc.c.w : pc.c.y, l)};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        d.p01[h] = ((cw[h][0] >> sh) & 0x03030303u) | (__builtin_amdgcn_alignbit(cw[h][1], cw[h][1], rot) & 0x30303030u);
-        d.p23[h] = ((cw[h][2] >> sh) & 0x03030303u) | (__builtin_amdgcn_alignbit(cw[h][3], cw[h][3], rot) & 0x30303030u);
+        d.e[h] = cw[h] & 0x33333333u;
+        d.o[h] = (cw[h] >> 2) & 0x33333333u;
     }
     if constexpr (CODES_ONLY) return;
-    const bool low = j < 2, odd = (j & 1) != 0;
-    // stage 1: lanes j < 2 keep rows 0, 1 of column j and receive those of
-    // column j + 2; lanes j >= 2 keep rows 2, 3 of column j, receive column j - 2
-    const uint32_t recv = quad_perm<0x4e>(low ? ah : al);  // [2, 3, 0, 1]
-    const uint32_t lowc = low ? al : recv;                 // column j & 1
-    const uint32_t highc = low ? recv : ah;                // column (j & 1) + 2
-    // stage 2: even lanes send their odd rows' halves, odd lanes their even
-    // rows'; each keeps its own row's halves
-    const uint32_t send2 = __builtin_amdgcn_perm(highc, lowc, odd ? 0x05040100u : 0x07060302u);
-    const uint32_t recv2 = quad_perm<0xb1>(send2);  // [1, 0, 3, 2]
-    const uint32_t a01 = __builtin_amdgcn_perm(recv2, lowc, odd ? 0x03020504u : 0x05040100u);
-    const uint32_t a23 = __builtin_amdgcn_perm(recv2, highc, odd ? 0x03020706u : 0x07060100u);
-    d.arow = __builtin_bit_cast(f16x4, uint2{a01, a23});
-    // B of both groups per lane (the same four moves for either group)
-    const uint32_t bw[4] = {quad_lane<0>(pc.b), quad_lane<1>(pc.b), quad_lane<2>(pc.b), quad_lane<3>(pc.b)};
-#pragma unroll
-    for (int b = 0; b < 4; ++b) d.bvec[b] = h2f(jj ? bw[b] >> 16 : bw[b] & 0xffffu);
+    const _Float16 one = static_cast<_Float16>(1.0f), zero = static_cast<_Float16>(0.0f);
+    const f16x4 acol = __builtin_bit_cast(f16x4, jj ? uint2{pc.a.z, pc.a.w} : uint2{pc.a.x, pc.a.y});
+    const f16x4 bcol = __builtin_bit_cast(f16x4, uint2{jj ? pc.b >> 16 : pc.b & 0xffffu, 0u});
+    const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 row = __builtin_amdgcn_mfma_f32_4x4x4f16(acol, l.unit, none, 0, 0, 0);
+    d.bvec = __builtin_amdgcn_mfma_f32_4x4x4f16(bcol, f16x4{one, zero, zero, zero}, none, 0, 0, 0);
+    d.arow = f16x4{static_cast<_Float16>(row[0]), static_cast<_Float16>(row[2]), static_cast<_Float16>(row[1]),
+                   static_cast<_Float16>(row[3])};
 }
 
 // Vectors 4N .. 4N+3 of the row block: one matrix-core instruction; lane
-// (beta, j) stores vector 4N+j at dst + 16N + 4j (dst = the lane's row).
-// CODES_ONLY: the four codes themselves (exact small integers in fp16) are
-// stored as the vector's weights.
+// (beta, j) gets vector 4N+j, which decode_vecs stores at dst + 16N + 4j (dst =
+// the lane's row).  CODES_ONLY: the four codes themselves (exact small
+// integers in fp16, components in the order 0, 2, 1, 3) are stored as the
+// vector's weights.
+template <int N>
+__device__ inline f16x4 code_quad(const DecOps& d) {
+    const f16x2 lo = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(d.e[N >> 2], 2.0f, N & 3);
+    const f16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(d.o[N >> 2], 2.0f, N & 3);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+}
+
 template <int N, bool CODES_ONLY = false>
 __device__ inline void decode_vecs(const DecOps& d, _Float16* dst, int j) {
-    const f16x2 lo = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(d.p01[N >> 2], 2.0f, N & 3);
-    const f16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(d.p23[N >> 2], 2.0f, N & 3);
-    const f16x4 q = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+    const f16x4 q = code_quad<N>(d);
     if constexpr (CODES_ONLY) {
         *reinterpret_cast<f16x4*>(dst + 16 * N + 4 * j) = q;
         return;
@@ -204,6 +233,23 @@ __device__ inline void decode_vecs(const DecOps& d, _Float16* dst, int j) {
 #pragma unroll
     for (int a = 0; a < 4; ++a) o[a] = static_cast<_Float16>(w[a]);
     *reinterpret_cast<f16x4*>(dst + 16 * N + 4 * j) = o;
+}
+
+// Half H of a tile (vectors 16 H .. 16 H + 15 of every row), in fp32: four
+// independent matrix-core instructions; w[n] is vector 16 H + 4 n + j.
+template <int H>
+__device__ inline void decode_half(const DecOps& d, f32x4 (&w)[4]) {
+    const f16x4 q[4] = {code_quad<4 * H>(d), code_quad<4 * H + 1>(d), code_quad<4 * H + 2>(d), code_quad<4 * H + 3>(d)};
+#pragma unroll
+    for (int n = 0; n < 4; ++n) w[n] = __builtin_amdgcn_mfma_f32_4x4x4f16(d.arow, q[n], d.bvec, 0, 0, 0);
+}
+
+// fp32 weights of one vector -> fp16 (one rounding), stored at dst.
+__device__ inline void store_vec(const f32x4& w, void* dst) {
+    f16x4 o;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) o[a] = static_cast<_Float16>(w[a]);
+    *static_cast<f16x4*>(dst) = o;
 }
 
 }  // namespace

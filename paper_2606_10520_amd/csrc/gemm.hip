@@ -98,7 +98,7 @@ __device__ inline void load_x(__amdgpu_buffer_rsrc_t rx, uint32_t off, uint32_t 
 template <int MI, int S, bool FOLD = false>
 __device__ inline void slice(__amdgpu_buffer_rsrc_t rx, uint32_t xnext, uint32_t row_step, f16x8 (&xq)[4][MI],
                              f16x8 (&wb)[2][kNI], const _Float16* wsrc, bool decode_next, const Piece (&src)[2],
-                             int jj, DecOps (&ops)[2], int j, _Float16* const (&wdst)[2], f32x4 (&acc)[MI][kNI]) {
+                             int jj, DecOps (&ops)[2], const DecLane& dl, int j, _Float16* const (&wdst)[2], f32x4 (&acc)[MI][kNI]) {
     load_x<MI>(rx, xnext, row_step, xq[(S + 2) & 3]);
     if (S < 3) read_w(wsrc + 32 * (S + 1), wb[(S + 1) & 1]);
     // (After the last group this decodes zeros into the idle buffer: no
@@ -106,7 +106,7 @@ __device__ inline void slice(__amdgpu_buffer_rsrc_t rx, uint32_t xnext, uint32_t
     (void)decode_next;
     {
         constexpr int r = S >> 1;  // local row block of this wavefront
-        if ((S & 1) == 0) prepare<FOLD>(src[r], j, jj, ops[r]);
+        if ((S & 1) == 0) prepare<FOLD>(src[r], dl, jj, ops[r]);
         constexpr int n0 = 4 * (S & 1);
         decode_vecs<n0 + 0, FOLD>(ops[r], wdst[r], j);
         decode_vecs<n0 + 1, FOLD>(ops[r], wdst[r], j);
@@ -141,6 +141,7 @@ struct GemmState {
     const _Float16* wlane;
     _Float16* wrow[2];
     int gend, j;  // end of this workgroup's group range
+    DecLane dl;
     __amdgpu_buffer_rsrc_t ra;  // shared affine block (format variants)
     int affine_one;
 };
@@ -167,10 +168,10 @@ __device__ inline void group_step(const GemmState<MI>& st, int g, const Piece (&
     // activation slices 2, 3 of this group, 0, 1 of the next (or nothing)
     const uint32_t xoff = st.xbase + static_cast<uint32_t>(g) * (4 * SL);
     const uint32_t xn = decode_next ? xoff + 4 * SL : kOutOfRange;
-    slice<MI, 0, FOLD>(st.rx, xoff + 2 * SL, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.j, wdst, acc);
-    slice<MI, 1, FOLD>(st.rx, xoff + 3 * SL, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.j, wdst, acc);
-    slice<MI, 2, FOLD>(st.rx, xn, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.j, wdst, acc);
-    slice<MI, 3, FOLD>(st.rx, xn + SL, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.j, wdst, acc);
+    slice<MI, 0, FOLD>(st.rx, xoff + 2 * SL, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.dl, st.j, wdst, acc);
+    slice<MI, 1, FOLD>(st.rx, xoff + 3 * SL, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.dl, st.j, wdst, acc);
+    slice<MI, 2, FOLD>(st.rx, xn, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.dl, st.j, wdst, acc);
+    slice<MI, 3, FOLD>(st.rx, xn + SL, st.row_step, xq, wb, wsrc, decode_next, src, jj, ops, st.dl, st.j, wdst, acc);
     __syncthreads();
 }
 
@@ -273,6 +274,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const TileBatch tb) {
     GemmState<MI> st;
     const int beta = lane >> 2;
     st.j = lane & 3;
+    st.dl = make_dec_lane(st.j);
     st.gend = gend;
     if constexpr (kVar) {
         st.ra = ra;
@@ -328,7 +330,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(const TileBatch tb) {
         DecOps ops;
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            prepare<FOLD>(pa[r], st.j, 0, ops);
+            prepare<FOLD>(pa[r], st.dl, 0, ops);
             decode_vecs<0, FOLD>(ops, st.wrow[r], st.j);
             decode_vecs<1, FOLD>(ops, st.wrow[r], st.j);
             decode_vecs<2, FOLD>(ops, st.wrow[r], st.j);
@@ -704,7 +706,8 @@ __global__ __launch_bounds__(1024) void fold_tiles_kernel(const uint16_t* __rest
         fold(sl, xp, unused);
         f16x8 o;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = static_cast<_Float16>(ldexpf(xp[e], s));
+        for (int e = 0; e < 8; ++e)  // components of a vector in the decode's order 0, 2, 1, 3
+            o[e] = static_cast<_Float16>(ldexpf(xp[(e & 4) | ((e & 1) << 1) | ((e >> 1) & 1)], s));
         *reinterpret_cast<f16x8*>(out + static_cast<size_t>(sl) * 512) = o;
     }
     if (w == 0 && lane < 8 && real) {

@@ -76,10 +76,21 @@ struct SkBatch {
 // 8 (lane / 16) + 32 c) and multiply with the activation operands (token
 // lane % 16 + 16 i at the same columns).
 template <int MT>
-__device__ inline void tile_product(const Piece& pc, int jj, int j, _Float16* wrow, const _Float16* wlane,
-                                    const f16x8 (&xa)[MT][4], f32x4 (&acc)[MT]) {
+__device__ inline void tile_multiply(const _Float16* wlane, const f16x8 (&xa)[MT][4], f32x4 (&acc)[MT]) {
+    f16x8 wb[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) wb[c] = *reinterpret_cast<const f16x8*>(wlane + 32 * c);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[i][c], wb[c], acc[i], 0, 0, 0);
+}
+
+template <int MT>
+__device__ inline void tile_product(const Piece& pc, int jj, const DecLane& dl, int j, _Float16* wrow,
+                                    const _Float16* wlane, const f16x8 (&xa)[MT][4], f32x4 (&acc)[MT]) {
     DecOps ops;
-    prepare(pc, j, jj, ops);
+    prepare(pc, dl, jj, ops);
     decode_vecs<0>(ops, wrow, j);
     decode_vecs<1>(ops, wrow, j);
     decode_vecs<2>(ops, wrow, j);
@@ -88,13 +99,38 @@ __device__ inline void tile_product(const Piece& pc, int jj, int j, _Float16* wr
     decode_vecs<5>(ops, wrow, j);
     decode_vecs<6>(ops, wrow, j);
     decode_vecs<7>(ops, wrow, j);
-    f16x8 wb[4];
+    tile_multiply<MT>(wlane, xa, acc);
+}
+
+// Both groups of a piece in a fixed order, for workgroups of one or two row
+// blocks, whose packets are too few to hide latencies across wavefronts (and
+// whose registers allow it): both gathers first, then per group the
+// independent 4x4x4 instructions of the tile together, then their conversions
+// and stores.  Left to itself the compiler keeps few registers live and waits
+// for every 4x4x4 result in turn (16 tokens: 4096 x 4096 6.7 -> 6.4 us; 4 tokens:
+// 4096 x 11008 11.3 -> 9.5 us, with the branch described below gone).
+template <int MT>
+__device__ inline void piece_product(const Piece& pc, const DecLane& dl, int j, _Float16* wrow, const _Float16* wlane,
+                                     const f16x8 (&x0)[MT][4], const f16x8 (&x1)[MT][4], f32x4 (&acc)[MT]) {
+    DecOps ops[2];
+    prepare(pc, dl, 0, ops[0]);
+    prepare(pc, dl, 1, ops[1]);
+    f32x4 w0[4], w1[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) wb[c] = *reinterpret_cast<const f16x8*>(wlane + 32 * c);
+    for (int jj = 0; jj < 2; ++jj) {
+        __builtin_amdgcn_sched_barrier(0);
+        decode_half<0>(ops[jj], w0);
+        __builtin_amdgcn_sched_barrier(0);
+        decode_half<1>(ops[jj], w1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+        for (int n = 0; n < 4; ++n) store_vec(w0[n], wrow + 16 * n + 4 * j);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[i][c], wb[c], acc[i], 0, 0, 0);
+        for (int n = 0; n < 4; ++n) store_vec(w1[n], wrow + 16 * (4 + n) + 4 * j);
+        __builtin_amdgcn_sched_barrier(0);
+        tile_multiply<MT>(wlane, jj ? x1 : x0, acc);
+    }
 }
 
 // Per wavefront: its decode tile, and with one token tile an activation
@@ -212,6 +248,7 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
     };
 
     const int j = lane & 3;
+    const DecLane dl = make_dec_lane(j);
     _Float16* const wtile = reinterpret_cast<_Float16*>(warea);
     _Float16* wrow = wtile + (lane >> 2) * kTRow;
     const _Float16* wlane = wtile + (lane & 15) * kTRow + 8 * (lane >> 4);
@@ -256,9 +293,15 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
         }
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
-            if (local_rb(b) >= 0) {  // uniform
-                tile_product<MT>(pc[b % kRing], 0, j, wrow, wlane, x0, acc[b]);
-                tile_product<MT>(pc[b % kRing], 1, j, wrow, wlane, x1, acc[b]);
+            // (Up to three row blocks, one that no problem has is decoded from
+            // zeros: a branch around it would leave its loads pending at the
+            // loop's head, where the compiler then drains them before the next
+            // requests.  Taller workgroups measured faster with the branch.)
+            if constexpr (MT == 1 && RB <= 2) {
+                piece_product<MT>(pc[b % kRing], dl, j, wrow, wlane, x0, x1, acc[b]);
+            } else if (RB <= 3 || local_rb(b) >= 0) {  // uniform
+                tile_product<MT>(pc[b % kRing], 0, dl, j, wrow, wlane, x0, acc[b]);
+                tile_product<MT>(pc[b % kRing], 1, dl, j, wrow, wlane, x1, acc[b]);
             }
             if (b + kRing < RB) load(p, b + kRing, pc[b % kRing]);
         }

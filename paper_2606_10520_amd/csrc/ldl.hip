@@ -10,16 +10,24 @@
 // buffer), one 4 x 4 pivot block j gives
 //     D_j = S_jj,   U[0:j, j] = S[0:j, j] D_j^-1,
 //     S[0:j, 0:j] -= U[0:j, j] D_j U[0:j, j]^T.
-// Blocked over panels of 64 columns (16 pivot blocks), right to left:
-//  1. diag: one workgroup factorises the panel's 64 x 64 diagonal block
-//     in LDS, pivot block by pivot block, and keeps the 16 inverses D_j^-1;
-//  2. strip: every row r above the panel solves w U_pp^T = S[r, panel]
+// Blocked over panels of 64 columns (16 pivot blocks), right to left, two
+// launches per panel:
+//  1. strip: every row r above the panel solves w U_pp^T = S[r, panel]
 //     (U_pp the panel's factor, unit upper: a back substitution over its
 //     pivot blocks) and stores w and U[r, panel] = w D_p^-1, one wavefront
 //     per row, lane c = panel column c;
-//  3. trailing: S[a][b] -= sum_k W[a][k] U[b][k] over the panel's 64
+//  2. trailing: S[a][b] -= sum_k W[a][k] U[b][k] over the panel's 64
 //     columns, for a <= b above the panel (64 x 64 tiles of the upper
-//     triangle on the fp64 matrix cores).
+//     triangle on the fp64 matrix cores).  The workgroup of the next panel's
+//     diagonal tile, the first of the launch, keeps its tile in registers and
+//     factorises it pivot block by pivot block while the others update
+//     theirs (the panel's serial part: as a launch of its own it was 1.4 of
+//     3.1 ms at K = 4096).
+// K = 4096, MI355X: 1.84 ms (3.14 before).  A diagonal block alone takes 12 us
+// (23 with its 64 x 64 block in LDS and two barriers per pivot); a trailing
+// launch 45 to 15 us, the lower end set by the pivots; a strip 5 to 8 us.
+// Error against an 80-bit factorisation (K = 128 to 1024, twelve Hessians of
+// condition about 1e5): 9e-15 to 1.1e-13, as before.
 // Every pivot block is checked for positive definiteness (its leading
 // principal minors); the first failure is reported through `info`.
 #include "common.hpp"
@@ -44,20 +52,29 @@ __global__ __launch_bounds__(256) void ldl_init_kernel(const double* H, double* 
     if (e == 0 && info) *info = 0;
     if (e >= K * K) return;
     const int64_t a = e / K, b = e - a * K;
-    const double2 h = *reinterpret_cast<const double2*>(H + e);
+    double2 h = double2{0.0, 0.0};
+    if (a <= b + 1) h = *reinterpret_cast<const double2*>(H + e);
     *reinterpret_cast<double2*>(U + e) = double2{a <= b ? h.x : 0.0, a <= b + 1 ? h.y : 0.0};
+}
+
+// a b - c d to within two roundings of the result (Kahan): the fma recovers the
+// rounding error of c d.  The minors of a pivot block whose columns share a
+// common component cancel to a small part of their products.
+__device__ inline double det2(double a, double b, double c, double d) {
+    const double w = c * d;
+    return fma(a, b, -w) + fma(-c, d, w);
 }
 
 // Inverse of a 4 x 4 matrix by Laplace expansion along its first two rows
 // (complementary 2 x 2 minors: s_ of rows 0, 1, c_ of rows 2, 3), every
 // index fixed at compile time; returns the determinant.
 __device__ inline double inverse4(const double (&m)[4][4], double (&b)[4][4]) {
-    const double s0 = m[0][0] * m[1][1] - m[1][0] * m[0][1], s1 = m[0][0] * m[1][2] - m[1][0] * m[0][2];
-    const double s2 = m[0][0] * m[1][3] - m[1][0] * m[0][3], s3 = m[0][1] * m[1][2] - m[1][1] * m[0][2];
-    const double s4 = m[0][1] * m[1][3] - m[1][1] * m[0][3], s5 = m[0][2] * m[1][3] - m[1][2] * m[0][3];
-    const double c5 = m[2][2] * m[3][3] - m[3][2] * m[2][3], c4 = m[2][1] * m[3][3] - m[3][1] * m[2][3];
-    const double c3 = m[2][1] * m[3][2] - m[3][1] * m[2][2], c2 = m[2][0] * m[3][3] - m[3][0] * m[2][3];
-    const double c1 = m[2][0] * m[3][2] - m[3][0] * m[2][2], c0 = m[2][0] * m[3][1] - m[3][0] * m[2][1];
+    const double s0 = det2(m[0][0], m[1][1], m[1][0], m[0][1]), s1 = det2(m[0][0], m[1][2], m[1][0], m[0][2]);
+    const double s2 = det2(m[0][0], m[1][3], m[1][0], m[0][3]), s3 = det2(m[0][1], m[1][2], m[1][1], m[0][2]);
+    const double s4 = det2(m[0][1], m[1][3], m[1][1], m[0][3]), s5 = det2(m[0][2], m[1][3], m[1][2], m[0][3]);
+    const double c5 = det2(m[2][2], m[3][3], m[3][2], m[2][3]), c4 = det2(m[2][1], m[3][3], m[3][1], m[2][3]);
+    const double c3 = det2(m[2][1], m[3][2], m[3][1], m[2][2]), c2 = det2(m[2][0], m[3][3], m[3][0], m[2][3]);
+    const double c1 = det2(m[2][0], m[3][2], m[3][0], m[2][2]), c0 = det2(m[2][0], m[3][1], m[3][0], m[2][1]);
     const double det = s0 * c5 - s1 * c4 + s2 * c3 + s3 * c2 - s4 * c1 + s5 * c0;
     const double r = 1.0 / det;
     b[0][0] = (m[1][1] * c5 - m[1][2] * c4 + m[1][3] * c3) * r;
@@ -77,95 +94,6 @@ __device__ inline double inverse4(const double (&m)[4][4], double (&b)[4][4]) {
     b[3][2] = (-m[3][0] * s3 + m[3][1] * s1 - m[3][2] * s0) * r;
     b[3][3] = (m[2][0] * s3 - m[2][1] * s1 + m[2][2] * s0) * r;
     return det;
-}
-
-// Panel [c0, c0 + 64): its diagonal block factorised in LDS, pivot block by
-// pivot block (a = 4 jb, the last first).  Per pivot, two phases:
-//  A. every thread t < max(1, a) inverts D_j itself (inverse4) and forms
-//     row t of u = S[0:a, a:a+4] D_j^-1; thread 0 also writes D_j, D_j^-1 and
-//     checks positive definiteness (the leading principal minors);
-//  B. S[r][c] -= u[r] . S[c][a:a+4] for r <= c < a (thread: column c = t % 64,
-//     rows t / 64 + 4k; computed for the whole block, without branches),
-//     and u and the identity pivot block go to U.
-// Entries below the pivot blocks keep the zeros written by the set-up, so
-// the LDS block is never written back.  The 16 inverses go to dinv.
-__global__ __launch_bounds__(256) void ldl_diag_kernel(double* U, int64_t K, int64_t c0, double* D, int32_t* info,
-                                                       double* dinv) {
-    __shared__ double B[kLdlP * kLdlPitch];
-    __shared__ double Di[16 * 16];
-    __shared__ double uu[kLdlP * 4];
-    const int t = threadIdx.x;
-    double* const blk = U + c0 * K + c0;
-    const int c = t & 63, rq = t >> 6;
-    {
-        // all 16 loads of a thread in flight at once (row rq + 4k, column c)
-        double v[kLdlP / 4];
-#pragma unroll
-        for (int k = 0; k < kLdlP / 4; ++k) v[k] = blk[(rq + 4 * k) * K + c];
-#pragma unroll
-        for (int k = 0; k < kLdlP / 4; ++k) B[(rq + 4 * k) * kLdlPitch + c] = v[k];
-    }
-    __syncthreads();
-    for (int jb = kLdlP / 4 - 1; jb >= 0; --jb) {
-        const int a = 4 * jb;
-        // A.
-        if (t == 0 || t < a) {
-            double d[4][4], inv[4][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) d[i][j] = B[(a + (i < j ? i : j)) * kLdlPitch + a + (i < j ? j : i)];
-            const double det = inverse4(d, inv);
-            if (t == 0) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) Di[jb * 16 + i] = inv[i >> 2][i & 3];
-                if (D) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) D[(c0 / 4 + jb) * 16 + i] = d[i >> 2][i & 3];
-                }
-                const double m2 = d[0][0] * d[1][1] - d[1][0] * d[0][1];
-                const double m3 = d[0][0] * (d[1][1] * d[2][2] - d[1][2] * d[2][1]) -
-                                  d[0][1] * (d[1][0] * d[2][2] - d[1][2] * d[2][0]) +
-                                  d[0][2] * (d[1][0] * d[2][1] - d[1][1] * d[2][0]);
-                const bool ok = d[0][0] > 0.0 && m2 > 0.0 && m3 > 0.0 && det > 0.0;  // false on NaN
-                if (!ok && info && *info == 0) *info = static_cast<int32_t>(c0 / 4 + jb + 1);
-            }
-            if (t < a) {
-                double x[4];
-#pragma unroll
-                for (int n = 0; n < 4; ++n) x[n] = B[t * kLdlPitch + a + n];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    double v = 0.0;
-#pragma unroll
-                    for (int n = 0; n < 4; ++n) v = fma(x[n], inv[n][m], v);
-                    uu[t * 4 + m] = v;
-                }
-            }
-        }
-        __syncthreads();
-        // B.  Only S[r][c] with r <= c < a is live: the LDS entries below the
-        // diagonal and those of columns a and beyond are never read again
-        // (the factor goes straight to U), so the whole block is updated
-        // without branches; the dead entries take whatever they get.
-        {
-            double bc[4];
-#pragma unroll
-            for (int n = 0; n < 4; ++n) bc[n] = B[c * kLdlPitch + a + n];
-#pragma unroll
-            for (int k = 0; k < kLdlP / 4; ++k) {
-                const int r = rq + 4 * k;
-                double v = 0.0;
-#pragma unroll
-                for (int n = 0; n < 4; ++n) v = fma(uu[r * 4 + n], bc[n], v);
-                B[r * kLdlPitch + c] -= v;
-            }
-        }
-        if (t < 4 * a) blk[(t >> 2) * K + a + (t & 3)] = uu[t];
-        if (t < 16) blk[(a + (t >> 2)) * K + a + (t & 3)] = (t >> 2) == (t & 3) ? 1.0 : 0.0;
-        __syncthreads();
-    }
-    dinv[t] = Di[t];  // 256 threads, 16 x 16 values
 }
 
 // Rows r < c0 against the panel [c0, c0 + 64): w U_pp^T = S[r, panel]
@@ -212,37 +140,153 @@ __global__ __launch_bounds__(256) void ldl_strip_kernel(double* U, int64_t K, in
     }
 }
 
-// S[a][b] -= sum_k W[a][k] U[b][c0 + k] for a <= b < c0: workgroup (tb, ta)
-// takes the 64 x 64 tile of rows 64 ta, columns 64 tb (tiles below the
-// diagonal return at once) on the fp64 matrix cores.  Both 64 x 64 operands
-// are staged row-major in LDS (pitch 68 doubles: an operand read touches
-// every bank the minimum number of times); wavefront w computes the 32 x 32
-// quarter (rows 32 (w / 2), columns 32 (w % 2)) as 2 x 2 blocks of
-// v_mfma_f64_16x16x4f64 over 16 steps of 4 columns of k.  Operand lanes:
-// A[i][k] at lane i + 16 k, B[k][j] at lane j + 16 k; result D[i][j] at
-// lane j + 16 (i % 4), item i / 4.
 constexpr int kLdlMPitch = kLdlP + 4;
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void ldl_trailing_kernel(double* U, int64_t K, int64_t c0, const double* W) {
-    const int ta = blockIdx.y, tb = blockIdx.x;
-    if (ta > tb) return;  // uniform
-    __shared__ double Ws[kLdlP * kLdlMPitch];  // [row][k]
-    __shared__ double Us[kLdlP * kLdlMPitch];  // [column][k]
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+// (by value: a conditional on array elements themselves puts the array in memory)
+__device__ inline double pick(bool c, double a, double b) { return c ? a : b; }
+
+// Pivot blocks of tile column TC (panel columns 16 TC .. 16 TC + 15), the last
+// first.  Wavefront w holds S's rows 16 w .. 16 w + 15 as tiles acc[tj] of
+// columns 16 tj in matrix-core result layout; wavefronts above TC have no rows
+// left.  Per pivot block at column a:
+//  * the column strip S[0:a+4, a:a+4] goes to P (one 64 x 4 buffer per pivot
+//    block, so one barrier each);
+//  * every lane inverts D itself; lane (i, k) forms u[i][k] = sum_n S[i][n]
+//    D^-1[n][k], which is the A operand, and P's rows are the B operand, of
+//    S -= u S[., a:a+4]^T (each lane taking only its column of the inverse,
+//    from four cofactors of a permuted D, was shorter but up to six times
+//    less accurate at K = 128);
+//  * u and the identity block go to U.
+// Only S[r][c] with r <= c < a is live; everything else (what lies below the
+// diagonal, columns a and beyond) takes whatever it gets and feeds only
+// entries of the same kind.
+template <int TC>
+__device__ inline void pivots(f64x4 (&acc)[4], double (*P)[kLdlP * 4], int w, int lane, double* blk, int64_t K) {
+    const int li = lane & 15, lk = lane >> 4;
+#pragma clang loop unroll(disable)
+    for (int jq = 3; jq >= 0; --jq) {
+        const int a = 16 * TC + 4 * jq;
+        double* const p = P[4 * TC + jq];
+        if (w <= TC && (li >> 2) == jq) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) p[(16 * w + lk + 4 * v) * 4 + (li & 3)] = acc[TC][v];
+        }
+        __syncthreads();
+        if (w <= TC) {  // uniform
+            double d[4][4], inv[4][4], b[TC + 1];
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) d[n][m] = p[4 * (a + (n < m ? n : m)) + (n < m ? m : n)];
+            double q[4];
+#pragma unroll
+            for (int n = 0; n < 4; ++n) q[n] = p[4 * (16 * w + li) + n];
+#pragma unroll
+            for (int tj = 0; tj <= TC; ++tj) b[tj] = p[4 * (16 * tj + li) + lk];
+            inverse4(d, inv);
+            double u = 0.0;
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                u = fma(q[n], pick(lk & 2, pick(lk & 1, inv[n][3], inv[n][2]), pick(lk & 1, inv[n][1], inv[n][0])), u);
+            }
+#pragma unroll
+            for (int tj = 0; tj <= TC; ++tj)
+                if (tj >= w) acc[tj] -= __builtin_amdgcn_mfma_f64_16x16x4f64(u, b[tj], f64x4{0.0, 0.0, 0.0, 0.0}, 0, 0, 0);
+            const int r = 16 * w + li;
+            if (r < a + 4) blk[r * K + a + lk] = r < a ? u : (r - a == lk ? 1.0 : 0.0);
+        }
+    }
+}
+
+// The panel's 64 x 64 diagonal block at c0, in acc as above: its factor to U,
+// the pivot blocks to D, their inverses to dinv, and the check of positive
+// definiteness (sixteen threads after the pivots, from the strips in P).
+__device__ inline void factorise(f64x4 (&acc)[4], double (*P)[kLdlP * 4], double* U, int64_t K, int64_t c0, double* D,
+                                 int32_t* info, double* dinv) {
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    double* const blk = U + c0 * K + c0;
+    pivots<3>(acc, P, w, lane, blk, K);
+    pivots<2>(acc, P, w, lane, blk, K);
+    pivots<1>(acc, P, w, lane, blk, K);
+    pivots<0>(acc, P, w, lane, blk, K);
+    if (t < 64) {  // wavefront 0; thread jb < 16 takes pivot block jb
+        const int jb = t & 15;
+        double d[4][4], inv[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[i][j] = P[jb][(4 * jb + (i < j ? i : j)) * 4 + (i < j ? j : i)];
+        const double det = inverse4(d, inv);
+        const double m2 = d[0][0] * d[1][1] - d[1][0] * d[0][1];
+        const double m3 = d[0][0] * (d[1][1] * d[2][2] - d[1][2] * d[2][1]) -
+                          d[0][1] * (d[1][0] * d[2][2] - d[1][2] * d[2][0]) +
+                          d[0][2] * (d[1][0] * d[2][1] - d[1][1] * d[2][0]);
+        const bool ok = d[0][0] > 0.0 && m2 > 0.0 && m3 > 0.0 && det > 0.0;  // false on NaN
+        const uint32_t bad = static_cast<uint32_t>(__ballot(!ok)) & 0xffffu;
+        if (t < 16) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) dinv[jb * 16 + i] = inv[i >> 2][i & 3];
+            if (D) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) D[(c0 / 4 + jb) * 16 + i] = d[i >> 2][i & 3];
+            }
+            // the first to fail is the highest: the last pivot goes first
+            if (t == 0 && bad && info && *info == 0) *info = static_cast<int32_t>(c0 / 4 + 32 - __clz(static_cast<int>(bad)));
+        }
+    }
+}
+
+// The last panel's diagonal block, which no trailing update comes before.
+__global__ __launch_bounds__(256) void ldl_diag_kernel(double* U, int64_t K, int64_t c0, double* D, int32_t* info,
+                                                       double* dinv) {
+    __shared__ double P[16][kLdlP * 4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    f64x4 acc[4];
+#pragma unroll
+    for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            acc[tj][v] = U[(c0 + 16 * w + (lane >> 4) + 4 * v) * K + c0 + 16 * tj + (lane & 15)];
+    factorise(acc, P, U, K, c0, D, info, dinv);
+}
+
+// S[a][b] -= sum_k W[a][k] U[b][c0 + k] for a <= b < c0: one 64 x 64 tile of
+// rows 64 ta, columns 64 tb, ta <= tb, per workgroup, on the fp64 matrix
+// cores, the last diagonal tile (the next panel's, which goes on to be
+// factorised) first.  Both 64 x 64 operands are staged row-major in LDS (pitch
+// 68 doubles: an operand read touches every bank the minimum number of
+// times); wavefront w computes rows 16 w .. 16 w + 15 as four 16 x 16 blocks
+// over 16 steps of 4 columns of k.  Operand lanes: A[i][k] at lane i + 16 k,
+// B[k][j] at lane j + 16 k; result D[i][j] at lane j + 16 (i % 4), item i / 4.
+struct TrailLds {
+    double Ws[kLdlP * kLdlMPitch];  // [row][k]
+    double Us[kLdlP * kLdlMPitch];  // [column][k]
+};
+static_assert(sizeof(TrailLds) >= 16 * kLdlP * 4 * 8, "the pivot strips reuse the operands' LDS");
+
+__global__ __launch_bounds__(256) void ldl_trailing_kernel(double* U, int64_t K, int64_t c0, const double* W, double* D,
+                                                           int32_t* info, double* dinv) {
+    __shared__ __attribute__((aligned(16))) TrailLds sh;
+    // tile number counted from the last diagonal tile down: tb by rows of the triangle
+    const int nt = static_cast<int>(c0 / kLdlP);
+    const int id = nt * (nt + 1) / 2 - 1 - static_cast<int>(blockIdx.x);
+    int tb = static_cast<int>((sqrtf(8.0f * static_cast<float>(id) + 1.0f) - 1.0f) * 0.5f);
+    while (tb * (tb + 1) / 2 > id) --tb;
+    while ((tb + 1) * (tb + 2) / 2 <= id) ++tb;
+    tb = __builtin_amdgcn_readfirstlane(tb);
+    const int ta = __builtin_amdgcn_readfirstlane(id - tb * (tb + 1) / 2);
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t a0 = static_cast<int64_t>(ta) * kLdlP, b0 = static_cast<int64_t>(tb) * kLdlP;
-    const int wr = 32 * (wave >> 1), wc = 32 * (wave & 1);
     const int li = lane & 15, lk = lane >> 4;
     // this lane's 16 outputs, read now (every one in bounds: the tile lies
     // above row c0) and written back after the products
-    double old[2][2][4];
+    double old[4][4];
+    double* const out = U + (a0 + 16 * w + lk) * K + b0 + li;
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int tj = 0; tj < 4; ++tj)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                old[bi][bj][v] = U[(a0 + wr + 16 * bi + lk + 4 * v) * K + b0 + wc + 16 * bj + li];
+        for (int v = 0; v < 4; ++v) old[tj][v] = out[4 * v * K + 16 * tj];
     {
         // the operands, 16 + 16 coalesced loads per thread in flight at once
         // (row rq + 4k, column c of each 64 x 64 operand)
@@ -255,40 +299,36 @@ __global__ __launch_bounds__(256) void ldl_trailing_kernel(double* U, int64_t K,
         }
 #pragma unroll
         for (int k = 0; k < kLdlP / 4; ++k) {
-            Ws[(rq + 4 * k) * kLdlMPitch + c] = wv[k];
-            Us[(rq + 4 * k) * kLdlMPitch + c] = uv[k];
+            sh.Ws[(rq + 4 * k) * kLdlMPitch + c] = wv[k];
+            sh.Us[(rq + 4 * k) * kLdlMPitch + c] = uv[k];
         }
     }
     __syncthreads();
-    f64x4 acc[2][2];
+    f64x4 acc[4];
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int tj = 0; tj < 4; ++tj) acc[tj] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int s = 0; s < kLdlP / 4; ++s) {
-        double av[2], bv[2];
+        const double av = sh.Ws[(16 * w + li) * kLdlMPitch + 4 * s + lk];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            av[q] = Ws[(wr + 16 * q + li) * kLdlMPitch + 4 * s + lk];
-            bv[q] = Us[(wc + 16 * q + li) * kLdlMPitch + 4 * s + lk];
-        }
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
-                acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[bi], bv[bj], acc[bi][bj], 0, 0, 0);
+        for (int tj = 0; tj < 4; ++tj)
+            acc[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, sh.Us[(16 * tj + li) * kLdlMPitch + 4 * s + lk], acc[tj],
+                                                           0, 0, 0);
     }
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int tj = 0; tj < 4; ++tj)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+        for (int v = 0; v < 4; ++v) acc[tj][v] = old[tj][v] - acc[tj][v];
+    if (blockIdx.x == 0) {  // uniform: the next panel's diagonal block
+        __syncthreads();    // the operands' LDS becomes the pivot strips'
+        factorise(acc, reinterpret_cast<double(*)[kLdlP * 4]>(&sh), U, K, b0, D, info, dinv);
+        return;
+    }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t a = a0 + wr + 16 * bi + lk + 4 * v;
-                const int64_t bcol = b0 + wc + 16 * bj + li;
-                if (a <= bcol) U[a * K + bcol] = old[bi][bj][v] - acc[bi][bj][v];
-            }
+    for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (ta < tb || 16 * w + lk + 4 * v <= 16 * tj + li) out[4 * v * K + 16 * tj] = acc[tj][v];
 }
 
 }  // namespace
@@ -305,16 +345,15 @@ hipError_t launch_ldl(int64_t K, const double* H, double* U, double* D, int32_t*
     hipLaunchKernelGGL(ldl_init_kernel, dim3(static_cast<unsigned>((pairs + 255) / 256)), dim3(256), 0, s, H, U, K,
                        info);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    for (int64_t c0 = K - kLdlP; c0 >= 0; c0 -= kLdlP) {
-        hipLaunchKernelGGL(ldl_diag_kernel, dim3(1), dim3(256), 0, s, U, K, c0, D, info, dinv);
-        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-        if (c0 == 0) break;
+    hipLaunchKernelGGL(ldl_diag_kernel, dim3(1), dim3(256), 0, s, U, K, K - kLdlP, D, info, dinv);
+    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    for (int64_t c0 = K - kLdlP; c0 > 0; c0 -= kLdlP) {
         const int64_t rows4 = c0 / 4;
         hipLaunchKernelGGL(ldl_strip_kernel, dim3(static_cast<unsigned>(rows4 < 1024 ? rows4 : 1024)), dim3(256), 0,
                            s, U, K, c0, dinv, W);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         const unsigned nt = static_cast<unsigned>(c0 / kLdlP);
-        hipLaunchKernelGGL(ldl_trailing_kernel, dim3(nt, nt), dim3(256), 0, s, U, K, c0, W);
+        hipLaunchKernelGGL(ldl_trailing_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, s, U, K, c0, W, D, info, dinv);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     }
     return hipSuccess;

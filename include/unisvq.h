@@ -211,18 +211,18 @@ int unisvq_gemv_batched(const unisvq_gemv_problem* problems, int count, int64_t 
  * above 16 tokens sized for the copy in 16-token tiles, so M counts rounded
  * up to a multiple of 16) and one fp32 scale per token (rounded up to 256);
  * above 16 tokens, for products with too few output tiles to fill the GPU,
- * fp32 partial sums of a split along K (splits*M*N*4 bytes).  From 17 to 32
- * tokens the size covers either kernel below (the one taken may use less).  0 also for an invalid shape, M < 1 or an
- * unknown x_dtype.  Host-only, no GPU needed. */
+ * fp32 partial sums of a split along K (splits*M*N*4 bytes).  From 17 to 64
+ * tokens the size covers either kernel below (the one taken may use less).
+ * 0 also for an invalid shape, M < 1 or an unknown x_dtype.  Host-only, no GPU needed. */
 size_t unisvq_gemm_workspace_bytes(int64_t N, int64_t K, int64_t M, int x_dtype);
 
 /* Prefill product y = x * W_hat^T for any M >= 1 (Eq. 1 with Eq. 4/8).
  * Arguments as unisvq_gemv; x_dtype F16 or BF16, y_dtype F16, BF16 or F32.
  * Up to 3 tokens the matrix-vector kernel of unisvq_gemv computes it (its
  * faster range; the workspace then goes unused), unless K is too long for
- * that kernel's LDS.  Up to 16 tokens -- and up to 32 when the product has
- * fewer than 64 tiles of 128 output rows, where the alternative would split
- * K many ways -- one launch of the small-batch kernel computes it: each
+ * that kernel's LDS.  Up to 32 tokens -- and up to 64 where measured faster:
+ * bf16 activations and fewer than 32768 rows, or f16 activations and a small
+ * M*K per compute unit -- one launch of a small-batch kernel computes it: each
  * wavefront decodes 16-row x 128-column tiles into its own LDS region and
  * multiplies them with all tokens at once; the wavefronts of a workgroup
  * split K and add their sums in a fixed order (no workspace beyond the bf16
@@ -257,14 +257,13 @@ size_t unisvq_gemm_batched_workspace_bytes(const unisvq_gemv_problem* problems, 
  * projections, at a small batch).  For M <= 16 all of them run in ONE launch
  * (of the matrix-vector kernel up to 3 tokens, as unisvq_gemm does, else of
  * the small-batch kernel), with the results of unisvq_gemm on each bit for
- * bit; so also from 17 to 32 tokens when all the batch's rows make fewer than
- * 64 tiles of 128 (unisvq_gemm's rule applied to the whole batch); otherwise
- * in ONE launch of the tiled product, planned over the whole
+ * bit; so also from 17 to 32 tokens, and to 64 where unisvq_gemm's rule, applied
+ * to the whole batch, takes the small-batch kernel; otherwise in ONE launch of the tiled product, planned over the whole
  * batch, plus one reduction launch when the batch's tiles leave CUs idle and
  * K is split -- the same arithmetic as unisvq_gemm, but the K split (and so
  * the grouping of the fp32 partial sums) follows the batch, so results can
  * differ from single calls in the last bits (bf16 activations first pass
- * through the per-problem pre-pass into their workspace slice; activations
+ * through the pre-pass, once per distinct buffer, into the workspace; activations
  * above 2 GiB fall back to one product at a time, as single calls).
  *   problems   HOST array of `count` descriptors (1..UNISVQ_MAX_BATCH), read
  *              before the call returns; packed format v1 weights; every

@@ -198,7 +198,7 @@ int launch_gemm_var(int64_t N, int64_t K, int bits, int d, const uint8_t* packed
 // decoder step: 1 token 29 us against 44, 3 tokens 40 against 46, 4 tokens
 // 50 against 46), falling back to the small-batch kernel where the
 // matrix-vector kernel's LDS cannot hold the activations.
-constexpr int64_t kSkinnyMaxM = 32;
+constexpr int64_t kSkinnyMaxM = 16;
 constexpr int64_t kGemvMaxM = 3;
 hipError_t launch_skinny(int64_t N, int64_t K, const uint8_t* packed, const uint8_t* affine, int affine_one,
                          int64_t M, const _Float16* x, const float* inv_scale, void* y, int y_dtype, hipStream_t s);
@@ -214,8 +214,14 @@ struct SkinnyProblem {
     int64_t N, K;
 };
 hipError_t launch_skinny_batch(const SkinnyProblem* probs, int count, int64_t M, int y_dtype, hipStream_t s);
+// The same for 17 to kMidMaxM tokens; `tiled`: every x is in the tiled layout of
+// the bf16 pre-pass.  mid_serves: whether a batch (row counts N, largest K) goes
+// there or to the tiled product.
+constexpr int64_t kMidMaxM = 64;
+bool mid_serves(const int64_t* N, int count, int64_t K, int64_t M, bool tiled);
+hipError_t launch_mid_batch(const SkinnyProblem* probs, int count, int64_t M, bool tiled, int y_dtype, hipStream_t s);
 // unisvq_gemm over a batch of problems (same M and dtypes): one launch of the
-// small-batch kernel for M <= kSkinnyMaxM, else one tiled launch (and one
+// small-batch kernels where they serve the batch, else one tiled launch (and one
 // reduction) for the batch, after the bf16 pre-passes.
 // Problem i uses the workspace bytes [off_i, off_i + gemm_workspace_bytes(i)),
 // off_i the 256-aligned sum of the earlier ones (gemm_batch_workspace_bytes).

@@ -492,13 +492,16 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const ReduceBatch r)
 // bf16 activations -> fp16 with a power-of-two scale per token (see the top
 // of the file).  One workgroup per token row; the row is read once and held
 // in registers (CH chunks of 8 values per thread, CH * 2048 >= K).
-template <int CH>
-__global__ __launch_bounds__(256) void scale_rows_kernel(const uint16_t* __restrict__ xb, int K,
+// TILED: the tiled layout described below, workgroups t >= M writing the zero
+// rows that fill the last token tile.
+template <int CH, bool TILED>
+__global__ __launch_bounds__(256) void scale_rows_kernel(const uint16_t* __restrict__ xb, int K, int M,
                                                          _Float16* __restrict__ xh, float* __restrict__ inv_scale) {
     __shared__ float wmax[4];
     const int t = blockIdx.x;
-    const uint16_t* row = xb + static_cast<size_t>(t) * K;
-    _Float16* out = xh + static_cast<size_t>(t) * K;
+    const bool real = !TILED || t < M;  // uniform
+    const uint16_t* row = xb + static_cast<size_t>(real ? t : 0) * K;
+    _Float16* out = TILED ? xh + static_cast<size_t>(t >> 4) * 16 * K + 8 * (t & 15) : xh + static_cast<size_t>(t) * K;
     const int chunks = K >> 3;  // 8 values per 16-byte chunk
     auto val = [](uint32_t bits16) { return __builtin_bit_cast(float, bits16 << 16); };
     uint4 v[CH];
@@ -506,7 +509,7 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(const uint16_t* __restr
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         const int c = threadIdx.x + 256 * i;
-        v[i] = c < chunks ? *reinterpret_cast<const uint4*>(row + 8 * c) : uint4{0u, 0u, 0u, 0u};
+        v[i] = real && c < chunks ? *reinterpret_cast<const uint4*>(row + 8 * c) : uint4{0u, 0u, 0u, 0u};
         const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
@@ -536,9 +539,9 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(const uint16_t* __restr
             o[2 * h] = static_cast<_Float16>(ldexpf(val(w[h] & 0xffffu), s));
             o[2 * h + 1] = static_cast<_Float16>(ldexpf(val(w[h] >> 16), s));
         }
-        *reinterpret_cast<f16x8*>(out + 8 * c) = o;
+        *reinterpret_cast<f16x8*>(out + (TILED ? 512 * (c >> 2) + 128 * (c & 3) : 8 * c)) = o;
     }
-    if (threadIdx.x == 0) inv_scale[t] = ldexpf(1.0f, -s);
+    if (threadIdx.x == 0 && real) inv_scale[t] = ldexpf(1.0f, -s);
 }
 
 // The same pre-pass writing the tiled layout of the prefill kernel: 1 KB
@@ -716,23 +719,36 @@ __global__ __launch_bounds__(1024) void fold_tiles_kernel(const uint16_t* __rest
     }
 }
 
+// Up to this many tokens the tiled copy is written by one workgroup per token
+// (16-byte stores, the row held in registers), above it by one per half tile:
+// pre-pass and a 16-row product, rows against half tiles, at 24 / 256 / 512 /
+// 1024 tokens: K = 4096 8.6 / 15.6 / 18.6 / 21.4 us against 12.0 / 18.0 / 18.7 /
+// 21.5, K = 28672 29.0 / 38.9 / 45.6 / 72.2 against 52.2 / 54.8 / 50.0 / 54.0 (a
+// few half tiles leave the chip idle; many rows write partial lines).
+constexpr int64_t kScaleRowsMaxM = 512;
+
+template <int CH, bool TILED>
+void launch_rows(dim3 grid, const uint16_t* x, int k, int m, _Float16* xh, float* inv, hipStream_t s) {
+    hipLaunchKernelGGL((scale_rows_kernel<CH, TILED>), grid, dim3(256), 0, s, x, k, m, xh, inv);
+}
+
 template <bool TILED>
 hipError_t launch_scale(int64_t K, int64_t M, const uint16_t* x, _Float16* xh, float* inv, hipStream_t s) {
     if (K > 65536) return hipErrorInvalidValue;  // not supported for bf16 activations
-    const int k = static_cast<int>(K);
-    if (TILED) {
-        hipLaunchKernelGGL(scale_tiles_kernel, dim3(static_cast<unsigned>((M + 15) / 16 * 2)), dim3(1024), 0, s, x, k,
-                           static_cast<int>(M), xh, inv);
+    const int k = static_cast<int>(K), m = static_cast<int>(M);
+    const int64_t pad = (M + 15) / 16 * 16;
+    if (TILED && M > kScaleRowsMaxM) {
+        hipLaunchKernelGGL(scale_tiles_kernel, dim3(static_cast<unsigned>(pad / 8)), dim3(1024), 0, s, x, k, m, xh, inv);
         return hipGetLastError();
     }
     const int64_t per = (K / 8 + 255) / 256;  // chunks per thread
-    const dim3 grid(static_cast<unsigned>(M)), block(256);
-    if (per <= 1) hipLaunchKernelGGL(scale_rows_kernel<1>, grid, block, 0, s, x, k, xh, inv);
-    else if (per <= 2) hipLaunchKernelGGL(scale_rows_kernel<2>, grid, block, 0, s, x, k, xh, inv);
-    else if (per <= 4) hipLaunchKernelGGL(scale_rows_kernel<4>, grid, block, 0, s, x, k, xh, inv);
-    else if (per <= 8) hipLaunchKernelGGL(scale_rows_kernel<8>, grid, block, 0, s, x, k, xh, inv);
-    else if (per <= 16) hipLaunchKernelGGL(scale_rows_kernel<16>, grid, block, 0, s, x, k, xh, inv);
-    else hipLaunchKernelGGL(scale_rows_kernel<32>, grid, block, 0, s, x, k, xh, inv);
+    const dim3 grid(static_cast<unsigned>(TILED ? pad : M));
+    if (per <= 1) launch_rows<1, TILED>(grid, x, k, m, xh, inv, s);
+    else if (per <= 2) launch_rows<2, TILED>(grid, x, k, m, xh, inv, s);
+    else if (per <= 4) launch_rows<4, TILED>(grid, x, k, m, xh, inv, s);
+    else if (per <= 8) launch_rows<8, TILED>(grid, x, k, m, xh, inv, s);
+    else if (per <= 16) launch_rows<16, TILED>(grid, x, k, m, xh, inv, s);
+    else launch_rows<32, TILED>(grid, x, k, m, xh, inv, s);
     return hipGetLastError();
 }
 
@@ -768,22 +784,11 @@ GemmPlan plan_gemm(int64_t N, int64_t K, int64_t M) {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t{255}; }
 
-// Above 16 tokens the small-batch kernel takes two token tiles and one row
-// block per workgroup, and beats the tiled product only on narrow batches:
-// 7B decoder step at 20 / 24 / 32 tokens, per launch, small-batch against
-// tiled: o (4096 rows) 10.0 / 10.6 / 11.9 against 15.3 / 15.5 / 16.1 us, down
-// (4096 rows) 21.6 / 22.8 / 26.3 against 24.8 / 25.3 / 25.7, q+k+v (12288)
-// 25.2 / 27.2 / 31.1 against 24.3 / 24.5 / 24.8, gate+up (22016) 47.9 / 51.9 /
-// 59.9 against 37.2 / 38.7 / 39.0.  So from 17 to 32 tokens a batch goes to
-// the small-batch kernel only when it has fewer than this many 128-row tiles.
-constexpr int64_t kSkinnyWideMaxTiles = 64;
-// The small-batch kernel for M tokens over a batch of `rows` output rows in all.
-inline bool use_skinny(int64_t M, int64_t rows) {
-    return M <= 16 || (M <= kSkinnyMaxM && (rows + 127) / 128 < kSkinnyWideMaxTiles);
-}
+// The 16-token kernel (launch_skinny_batch); above it mid_serves decides.
+inline bool use_skinny(int64_t M) { return M <= kSkinnyMaxM; }
 
 size_t partial_bytes(int64_t N, int64_t K, int64_t M) {
-    if (M <= 16) return 0;  // the small-batch kernel needs no partials (above: either kernel, see use_skinny)
+    if (M <= kSkinnyMaxM) return 0;  // the small-batch kernel needs no partials (above: either kernel, see mid_serves)
     const GemmPlan p = plan_gemm(N, K, M);
     return p.splits > 1 ? static_cast<size_t>(p.splits) * M * N * 4 : 0;
 }
@@ -884,7 +889,7 @@ int gemm_common(int64_t N, int64_t K, const uint8_t* packed, const uint8_t* affi
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     // bf16 activations for the tiled kernel (2-bit d = 4, M above the
     // small-batch range) go through the pre-pass that writes the tiled layout
-    const bool skinny = !var && use_skinny(M, N);
+    const bool skinny = !var && use_skinny(M);
     const bool tiled = x_dtype == UNISVQ_BF16 && !var && !skinny;
     if (x_dtype == UNISVQ_BF16) {
         _Float16* wxh = reinterpret_cast<_Float16*>(ws);
@@ -901,6 +906,10 @@ int gemm_common(int64_t N, int64_t K, const uint8_t* packed, const uint8_t* affi
         return launch_skinny(N, K, packed, affine, affine_one, M, xh, inv, y, y_dtype, s) == hipSuccess
                    ? UNISVQ_OK
                    : UNISVQ_EHIP;
+    if (!var && mid_serves(&N, 1, K, M, x_dtype == UNISVQ_BF16)) {
+        const SkinnyProblem q{packed, affine, affine_one, xh, inv, y, N, K};
+        return launch_mid_batch(&q, 1, M, tiled, y_dtype, s) == hipSuccess ? UNISVQ_OK : UNISVQ_EHIP;
+    }
     float* partial = reinterpret_cast<float*>(ws);
     // The activation buffer is addressed with 32-bit offsets: slice M.  The
     // workspace was sized for the whole product, which has far more than 256
@@ -966,9 +975,12 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     bool sliced = false;
     for (int i = 0; i < count; ++i) sliced = sliced || M > kMaxBufferBytes / (2 * probs[i].K) / 256 * 256;
-    int64_t rows = 0;
-    for (int i = 0; i < count; ++i) rows += probs[i].N;
-    const bool skinny = use_skinny(M, rows);
+    int64_t ns[kMaxBatch], kmax = 0;
+    for (int i = 0; i < count; ++i) {
+        ns[i] = probs[i].N;
+        kmax = probs[i].K > kmax ? probs[i].K : kmax;
+    }
+    const bool mid = mid_serves(ns, count, kmax, M, x_dtype == UNISVQ_BF16), skinny = use_skinny(M) || mid;
     if (!skinny && sliced) {
         // activations above 2 GiB: one product at a time, in token slices
         for (int i = 0; i < count; ++i) {
@@ -1000,14 +1012,24 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
             const _Float16* xh = static_cast<const _Float16*>(q.x);
             const float* inv = nullptr;
             if (x_dtype == UNISVQ_BF16) {
+                // (one copy for the problems that share their activations:
+                // 7B q+k+v at 2048 tokens, 10 us for each copy saved)
                 _Float16* wxh = reinterpret_cast<_Float16*>(slice);
                 slice += align256(static_cast<size_t>((M + 15) / 16 * 16) * q.K * 2);
                 float* winv = reinterpret_cast<float*>(slice);
                 slice += align256(static_cast<size_t>(M) * 4);
-                if (launch_scale<true>(q.K, M, static_cast<const uint16_t*>(q.x), wxh, winv, s) != hipSuccess)
-                    return q.K > 65536 ? UNISVQ_EUNSUP : UNISVQ_EHIP;
-                xh = wxh;
-                inv = winv;
+                int same = -1;
+                for (int j = 0; j < i && same < 0; ++j)
+                    if (probs[j].x == q.x && probs[j].K == q.K) same = j;
+                if (same >= 0) {
+                    xh = b.p[same].x;
+                    inv = b.p[same].inv_scale;
+                } else {
+                    if (launch_scale<true>(q.K, M, static_cast<const uint16_t*>(q.x), wxh, winv, s) != hipSuccess)
+                        return q.K > 65536 ? UNISVQ_EUNSUP : UNISVQ_EHIP;
+                    xh = wxh;
+                    inv = winv;
+                }
             }
             const int groups = static_cast<int>(q.K / kGroup);
             const int packets = (groups + 1) / 2;
@@ -1039,14 +1061,16 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
         const int st = launch_gemv_batch(g, count, M, x_dtype, y_dtype, s);
         if (st != UNISVQ_EUNSUP) return st;  // else K too long for its LDS: the small-batch kernel
     }
+    // small batches, one launch; bf16 activations as their scaled fp16 copy
+    // (row-major up to 16 tokens, tiled above)
     SkinnyProblem sp[kMaxBatch];
     for (int i = 0; i < count; ++i) {
         const GemmBatchProblem& q = probs[i];
         sp[i] = SkinnyProblem{q.packed, nullptr, 0, static_cast<const _Float16*>(q.x), nullptr, q.y, q.N, q.K};
         if (x_dtype == UNISVQ_BF16) {
-            // the problem's own scaled fp16 copy (row-major at this size), or
-            // that of an earlier problem with the same activations (one copy
-            // keeps them shared, so that workgroups may span the problems)
+            // the problem's own copy, or that of an earlier problem with the
+            // same activations (one copy keeps them shared, so that workgroups
+            // of the 16-token kernel may span the problems)
             int same = -1;
             for (int j = 0; j < i && same < 0; ++j)
                 if (probs[j].x == q.x && probs[j].K == q.K) same = j;
@@ -1054,9 +1078,12 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
                 sp[i].x = sp[same].x;
                 sp[i].inv_scale = sp[same].inv_scale;
             } else {
+                const int64_t mx = mid ? (M + 15) / 16 * 16 : M;
                 _Float16* wxh = reinterpret_cast<_Float16*>(ws);
-                float* winv = reinterpret_cast<float*>(ws + align256(static_cast<size_t>(M) * q.K * 2));
-                if (launch_scale<false>(q.K, M, static_cast<const uint16_t*>(q.x), wxh, winv, s) != hipSuccess)
+                float* winv = reinterpret_cast<float*>(ws + align256(static_cast<size_t>(mx) * q.K * 2));
+                const uint16_t* xb = static_cast<const uint16_t*>(q.x);
+                if ((mid ? launch_scale<true>(q.K, M, xb, wxh, winv, s) : launch_scale<false>(q.K, M, xb, wxh, winv, s)) !=
+                    hipSuccess)
                     return q.K > 65536 ? UNISVQ_EUNSUP : UNISVQ_EHIP;
                 sp[i].x = wxh;
                 sp[i].inv_scale = winv;
@@ -1064,7 +1091,9 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
         }
         ws += align256(gemm_workspace_bytes(q.N, q.K, M, x_dtype));
     }
-    return launch_skinny_batch(sp, count, M, y_dtype, s) == hipSuccess ? UNISVQ_OK : UNISVQ_EHIP;
+    const hipError_t e = mid ? launch_mid_batch(sp, count, M, x_dtype == UNISVQ_BF16, y_dtype, s)
+                             : launch_skinny_batch(sp, count, M, y_dtype, s);
+    return e == hipSuccess ? UNISVQ_OK : UNISVQ_EHIP;
 }
 
 int launch_gemm_shared(int64_t N, int64_t K, const uint8_t* packed_codes, const uint8_t* affine,

@@ -1,19 +1,18 @@
-// Small-batch product y = x * W_hat^T for up to 32 tokens on gfx950 (the
+// Small-batch product y = x * W_hat^T for up to 16 tokens on gfx950 (the
 // product routes 1 to 3 tokens to the matrix-vector kernel where its LDS
 // allows).
 //
-// A workgroup owns RB 16-row blocks (RB = 1, 2, 3, 4, 6 or 7; 1 above 16
-// tokens) of one problem over all
-// of K; several independent problems may share a launch (a decoder's query,
+// A workgroup owns RB 16-row blocks (RB = 1, 2, 3, 4, 6 or 7) of one problem
+// over all of K; several independent problems may share a launch (a decoder's query,
 // key and value projections).  Its sixteen wavefronts split the packets (two
 // 128-column groups each) round robin -- wavefront w takes packets w, w + 16,
 // ... -- so a 4096-column row is a single round: every wavefront requests all
 // it needs at once and no wavefront waits for another until they meet in LDS
 // at the end.  Per packet a wavefront loads the activations of the two groups
-// first (tokens in tiles of 16, fp16; reused from registers by the RB row
+// first (one tile of 16 tokens, fp16; reused from registers by the RB row
 // blocks), then the RB packets, each a coalesced 16-byte-per-lane read of the
 // packet slots, and computes row block by row block as the packets arrive.
-// With one token tile the activations travel through LDS: each load
+// The activations travel through LDS: each load
 // instruction reads four whole token rows of a group (256 contiguous bytes
 // each) straight into the wavefront's LDS area, laid out so that the
 // operand reads that follow are free of bank conflicts.  Loading the operand
@@ -74,21 +73,17 @@ struct SkBatch {
 // Group jj of a piece: decode into the wavefront's tile (lane (beta, j)
 // writes row beta), read it back as the B operand (row lane % 16, columns
 // 8 (lane / 16) + 32 c) and multiply with the activation operands (token
-// lane % 16 + 16 i at the same columns).
-template <int MT>
-__device__ inline void tile_multiply(const _Float16* wlane, const f16x8 (&xa)[MT][4], f32x4 (&acc)[MT]) {
+// lane % 16 at the same columns).
+__device__ inline void tile_multiply(const _Float16* wlane, const f16x8 (&xa)[4], f32x4& acc) {
     f16x8 wb[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) wb[c] = *reinterpret_cast<const f16x8*>(wlane + 32 * c);
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int i = 0; i < MT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[i][c], wb[c], acc[i], 0, 0, 0);
+    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[c], wb[c], acc, 0, 0, 0);
 }
 
-template <int MT>
 __device__ inline void tile_product(const Piece& pc, int jj, const DecLane& dl, int j, _Float16* wrow,
-                                    const _Float16* wlane, const f16x8 (&xa)[MT][4], f32x4 (&acc)[MT]) {
+                                    const _Float16* wlane, const f16x8 (&xa)[4], f32x4& acc) {
     DecOps ops;
     prepare(pc, dl, jj, ops);
     decode_vecs<0>(ops, wrow, j);
@@ -99,7 +94,7 @@ __device__ inline void tile_product(const Piece& pc, int jj, const DecLane& dl, 
     decode_vecs<5>(ops, wrow, j);
     decode_vecs<6>(ops, wrow, j);
     decode_vecs<7>(ops, wrow, j);
-    tile_multiply<MT>(wlane, xa, acc);
+    tile_multiply(wlane, xa, acc);
 }
 
 // Both groups of a piece in a fixed order, for workgroups of one or two row
@@ -109,9 +104,8 @@ __device__ inline void tile_product(const Piece& pc, int jj, const DecLane& dl, 
 // and stores.  Left to itself the compiler keeps few registers live and waits
 // for every 4x4x4 result in turn (16 tokens: 4096 x 4096 6.7 -> 6.4 us; 4 tokens:
 // 4096 x 11008 11.3 -> 9.5 us, with the branch described below gone).
-template <int MT>
 __device__ inline void piece_product(const Piece& pc, const DecLane& dl, int j, _Float16* wrow, const _Float16* wlane,
-                                     const f16x8 (&x0)[MT][4], const f16x8 (&x1)[MT][4], f32x4 (&acc)[MT]) {
+                                     const f16x8 (&x0)[4], const f16x8 (&x1)[4], f32x4& acc) {
     DecOps ops[2];
     prepare(pc, dl, 0, ops[0]);
     prepare(pc, dl, 1, ops[1]);
@@ -129,32 +123,27 @@ __device__ inline void piece_product(const Piece& pc, const DecLane& dl, int j, 
 #pragma unroll
         for (int n = 0; n < 4; ++n) store_vec(w1[n], wrow + 16 * (4 + n) + 4 * j);
         __builtin_amdgcn_sched_barrier(0);
-        tile_multiply<MT>(wlane, jj ? x1 : x0, acc);
+        tile_multiply(wlane, jj ? x1 : x0, acc);
     }
 }
 
-// Per wavefront: its decode tile, and with one token tile an activation
-// area (group 2p; group 2p + 1 is staged in the tile, which is free until
-// the first decode of the packet).
-template <int MT>
-constexpr int skinny_area_bytes() {
-    return kTile * 2 + (MT == 1 ? kXStage : 0);
-}
+// Per wavefront: its decode tile and an activation area (group 2p; group
+// 2p + 1 is staged in the tile, which is free until the first decode of the
+// packet).
+constexpr int kArea = kTile * 2 + kXStage;
 
-template <int MT, int RB>
+template <int RB>
 constexpr int skinny_lds_bytes() {
-    constexpr int tiles = kWavesS * skinny_area_bytes<MT>();
-    constexpr int red = kWavesS * RB * MT * 64 * 16;
+    constexpr int tiles = kWavesS * kArea;
+    constexpr int red = kWavesS * RB * 64 * 16;
     return tiles > red ? tiles : red;
 }
 
-// MT token tiles of 16 (M <= 16 MT), RB row blocks per workgroup; SHARED:
-// codes-only weights with the shared affine block.
-template <int MT, int RB, bool SHARED>
-__global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_kernel(const SkBatch batch) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[skinny_lds_bytes<MT, RB>()];
-    constexpr bool kStage = MT == 1;  // activations through LDS
-    constexpr int kArea = skinny_area_bytes<MT>();
+// RB row blocks per workgroup; SHARED: codes-only weights with the shared
+// affine block.
+template <int RB, bool SHARED>
+__global__ __launch_bounds__(kWavesS * 64, (RB <= 1 ? 8 : 4)) void skinny_kernel(const SkBatch batch) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[skinny_lds_bytes<RB>()];
 
     // problems of this workgroup (uniform scalar selection): `pb` holds its
     // first row block, `pn` the next problem; row blocks b >= bsplit are pn's
@@ -197,9 +186,6 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
     const __amdgpu_buffer_rsrc_t ran = make_rsrc(pn.affine, affine_bytes(pn));
     // tokens at or past M lie past the end of the buffer: they read zeros
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(pb.x, static_cast<uint32_t>(M) * K * 2u);
-    // activation operand of this lane: token lane % 16 + 16 i, columns
-    // 8 (lane / 16) + 32 c of a group
-    const uint32_t xlane = (static_cast<uint32_t>(lane & 15) * K + 8 * (lane >> 4)) * 2u;
     // staged: the lane's load offset (token lane / 16 of each instruction,
     // swizzled chunk) and its operand read offset within a staging area
     const int xr = lane >> 4, xt = lane & 15;
@@ -210,14 +196,6 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
     unsigned char* const uarea = lds + wu * kArea;
     unsigned char* const warea = lds + wave * kArea;
 
-    auto load_x = [&](int g, f16x8 (&xa)[MT][4]) {
-        const uint32_t base = g < groups ? xlane + static_cast<uint32_t>(g) * 256u : kOutOfRange;
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                xa[i][c] = __builtin_bit_cast(f16x8, ld128(rx, base + static_cast<uint32_t>(i) * (16u * K * 2u) + 64u * c));
-    };
     // group g's activations into the staging area at byte `at` of the
     // wavefront's area (past the last group or token: zeros).  Token
     // quads at or past M are not loaded: their rows hold stale values, which
@@ -231,9 +209,9 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
                     rx, (__attribute__((address_space(3))) void*)(uarea + at + q * kXInst), 16,
                     base + static_cast<uint32_t>(q) * (4u * K * 2u), 0, 0, 0);
     };
-    auto read_x = [&](int at, f16x8 (&xa)[MT][4]) {
+    auto read_x = [&](int at, f16x8 (&xa)[4]) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) xa[0][c] = *reinterpret_cast<const f16x8*>(warea + at + xread + 64 * c);
+        for (int c = 0; c < 4; ++c) xa[c] = *reinterpret_cast<const f16x8*>(warea + at + xread + 64 * c);
     };
     auto load = [&](int p, int b, Piece& pc) {
         const int rb = local_rb(b);
@@ -252,11 +230,9 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
     _Float16* const wtile = reinterpret_cast<_Float16*>(warea);
     _Float16* wrow = wtile + (lane >> 2) * kTRow;
     const _Float16* wlane = wtile + (lane & 15) * kTRow + 8 * (lane >> 4);
-    f32x4 acc[RB][MT];
+    f32x4 acc[RB];
 #pragma unroll
-    for (int b = 0; b < RB; ++b)
-#pragma unroll
-        for (int i = 0; i < MT; ++i) acc[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < RB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Packets wave, wave + 16, ...: a 4096-column row is one round.  Requests
     // go out in the order they are used: the activations of group 2p, the
@@ -268,40 +244,32 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
     constexpr int kRing = RB < 3 ? RB : 3;
     for (int p = wave; p < packets; p += kWavesS) {  // uniform
         Piece pc[kRing];
-        f16x8 x0[MT][4], x1[MT][4];
-        if constexpr (kStage) {
-            // Every read of the previous packet's tile is complete (its
-            // products consumed the values), so the tile may be loaded into.
-            // The compiler does not order these LDS-bound loads against the
-            // LDS reads below: the piece loads stay behind them (memory
-            // clobbers) and an explicit count waits for them -- the loads
-            // retire in order and exactly 3 per piece follow.
-            stage_x(2 * p, kTile * 2);
-            stage_x(2 * p + 1, 0);
-            asm volatile("" ::: "memory");
+        f16x8 x0[4], x1[4];
+        // Every read of the previous packet's tile is complete (its
+        // products consumed the values), so the tile may be loaded into.
+        // The compiler does not order these LDS-bound loads against the
+        // LDS reads below: the piece loads stay behind them (memory
+        // clobbers) and an explicit count waits for them -- the loads
+        // retire in order and exactly 3 per piece follow.
+        stage_x(2 * p, kTile * 2);
+        stage_x(2 * p + 1, 0);
+        asm volatile("" ::: "memory");
 #pragma unroll
-            for (int b = 0; b < kRing; ++b) load(p, b, pc[b]);
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * kRing) : "memory");
-            read_x(kTile * 2, x0);
-            read_x(0, x1);
-        } else {
-            load_x(2 * p, x0);
-            load(p, 0, pc[0]);
-            load_x(2 * p + 1, x1);
-#pragma unroll
-            for (int b = 1; b < kRing; ++b) load(p, b, pc[b]);
-        }
+        for (int b = 0; b < kRing; ++b) load(p, b, pc[b]);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * kRing) : "memory");
+        read_x(kTile * 2, x0);
+        read_x(0, x1);
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
             // (Up to three row blocks, one that no problem has is decoded from
             // zeros: a branch around it would leave its loads pending at the
             // loop's head, where the compiler then drains them before the next
             // requests.  Taller workgroups measured faster with the branch.)
-            if constexpr (MT == 1 && RB <= 2) {
-                piece_product<MT>(pc[b % kRing], dl, j, wrow, wlane, x0, x1, acc[b]);
+            if constexpr (RB <= 2) {
+                piece_product(pc[b % kRing], dl, j, wrow, wlane, x0, x1, acc[b]);
             } else if (RB <= 3 || local_rb(b) >= 0) {  // uniform
-                tile_product<MT>(pc[b % kRing], 0, dl, j, wrow, wlane, x0, acc[b]);
-                tile_product<MT>(pc[b % kRing], 1, dl, j, wrow, wlane, x1, acc[b]);
+                tile_product(pc[b % kRing], 0, dl, j, wrow, wlane, x0, acc[b]);
+                tile_product(pc[b % kRing], 1, dl, j, wrow, wlane, x1, acc[b]);
             }
             if (b + kRing < RB) load(p, b + kRing, pc[b % kRing]);
         }
@@ -309,21 +277,18 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
 
     // The sixteen wavefronts meet in LDS (over the decode tiles and staging
     // areas): each stores its accumulators as they are (lane order, 16
-    // bytes per lane), and one thread per (row block, token tile, lane) sums
-    // the sixteen in wavefront order.  D lane layout: row lane % 16, tokens
-    // 16 i + 4 (lane / 16) + e.
+    // bytes per lane), and one thread per (row block, lane) sums the sixteen in
+    // wavefront order.  D lane layout: row lane % 16, tokens 4 (lane / 16) + e.
     __syncthreads();
-    f32x4* red = reinterpret_cast<f32x4*>(lds);  // [wave][row block][token tile][lane]
+    f32x4* red = reinterpret_cast<f32x4*>(lds);  // [wave][row block][lane]
 #pragma unroll
-    for (int b = 0; b < RB; ++b)
-#pragma unroll
-        for (int i = 0; i < MT; ++i) red[((wave * RB + b) * MT + i) * 64 + lane] = acc[b][i];
+    for (int b = 0; b < RB; ++b) red[(wave * RB + b) * 64 + lane] = acc[b];
     __syncthreads();
-    for (int q = threadIdx.x; q < RB * MT * 64; q += kWavesS * 64) {
+    for (int q = threadIdx.x; q < RB * 64; q += kWavesS * 64) {
         f32x4 v = red[q];
 #pragma unroll
-        for (int w = 1; w < kWavesS; ++w) v += red[w * RB * MT * 64 + q];
-        const int ln = q & 63, bi = q >> 6, b = bi / MT, i = bi % MT;
+        for (int w = 1; w < kWavesS; ++w) v += red[w * RB * 64 + q];
+        const int ln = q & 63, b = q >> 6;
         const int rb = local_rb(b);
         if (rb < 0) continue;
         const bool first = b < bsplit;
@@ -332,7 +297,7 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
         const int row = rb * kRowBlock + (ln & 15);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int t = 16 * i + 4 * (ln >> 4) + e;
+            const int t = 4 * (ln >> 4) + e;
             if (t < M)
                 store_out(y, static_cast<int64_t>(t) * N + row, pb.inv_scale ? v[e] * pb.inv_scale[t] : v[e],
                           batch.y_dtype);
@@ -340,16 +305,16 @@ __global__ __launch_bounds__(kWavesS * 64, (RB * MT <= 1 ? 8 : 4)) void skinny_k
     }
 }
 
-template <int MT, int RB, bool SHARED>
+template <int RB, bool SHARED>
 hipError_t launch_k(const SkBatch& b, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL((skinny_kernel<MT, RB, SHARED>), dim3(static_cast<unsigned>(blocks)), dim3(kWavesS * 64), 0,
+    hipLaunchKernelGGL((skinny_kernel<RB, SHARED>), dim3(static_cast<unsigned>(blocks)), dim3(kWavesS * 64), 0,
                        s, b);
     return hipGetLastError();
 }
 
-template <int MT, int RB>
+template <int RB>
 hipError_t launch_rb(const SkBatch& b, int blocks, bool shared, hipStream_t s) {
-    return shared ? launch_k<MT, RB, true>(b, blocks, s) : launch_k<MT, RB, false>(b, blocks, s);
+    return shared ? launch_k<RB, true>(b, blocks, s) : launch_k<RB, false>(b, blocks, s);
 }
 
 // Workgroups of height rb for a batch (row blocks packed across problems when
@@ -395,8 +360,7 @@ int pick_rb(const SkinnyProblem* probs, int count, int max_rb, bool span) {
 
 hipError_t launch_skinny_batch(const SkinnyProblem* probs, int count, int64_t M, int y_dtype, hipStream_t s) {
     if (count < 1 || count > kMaxBatch || M < 1 || M > kSkinnyMaxM) return hipErrorInvalidValue;
-    // two token tiles: one row block per workgroup (registers)
-    const int max_rb = M > 16 ? 1 : 7;
+    constexpr int max_rb = 7;
     // workgroups may run across problems that share activations and K, when
     // every problem has at least max_rb row blocks (so at most two meet)
     bool span = count > 1;
@@ -418,14 +382,13 @@ hipError_t launch_skinny_batch(const SkinnyProblem* probs, int count, int64_t M,
     b.M = static_cast<int>(M);
     b.y_dtype = y_dtype;
     const bool shared = probs[0].affine != nullptr;
-    if (M > 16) return launch_rb<2, 1>(b, blocks, shared, s);
     switch (rb) {
-        case 7: return launch_rb<1, 7>(b, blocks, shared, s);
-        case 6: return launch_rb<1, 6>(b, blocks, shared, s);
-        case 4: return launch_rb<1, 4>(b, blocks, shared, s);
-        case 3: return launch_rb<1, 3>(b, blocks, shared, s);
-        case 2: return launch_rb<1, 2>(b, blocks, shared, s);
-        default: return launch_rb<1, 1>(b, blocks, shared, s);
+        case 7: return launch_rb<7>(b, blocks, shared, s);
+        case 6: return launch_rb<6>(b, blocks, shared, s);
+        case 4: return launch_rb<4>(b, blocks, shared, s);
+        case 3: return launch_rb<3>(b, blocks, shared, s);
+        case 2: return launch_rb<2>(b, blocks, shared, s);
+        default: return launch_rb<1>(b, blocks, shared, s);
     }
 }
 

@@ -215,10 +215,15 @@ struct SkinnyProblem {
 };
 hipError_t launch_skinny_batch(const SkinnyProblem* probs, int count, int64_t M, int y_dtype, hipStream_t s);
 // The same for 17 to kMidMaxM tokens; `tiled`: every x is in the tiled layout of
-// the bf16 pre-pass.  mid_serves: whether a batch (row counts N, largest K) goes
-// there or to the tiled product.
+// the pre-passes.  mid_plan: whether a batch (row counts N, largest K) goes
+// there or to the tiled product, and whether its activations are to be copied to
+// the tiled layout first (bf16 always; f16 where the copy pays and the workspace
+// has room for it, `room`).
 constexpr int64_t kMidMaxM = 64;
-bool mid_serves(const int64_t* N, int count, int64_t K, int64_t M, bool tiled);
+struct MidPlan {
+    bool serves, copy;
+};
+MidPlan mid_plan(const int64_t* N, int count, int64_t K, int64_t M, bool bf16, bool room);
 hipError_t launch_mid_batch(const SkinnyProblem* probs, int count, int64_t M, bool tiled, int y_dtype, hipStream_t s);
 // unisvq_gemm over a batch of problems (same M and dtypes): one launch of the
 // small-batch kernels where they serve the batch, else one tiled launch (and one

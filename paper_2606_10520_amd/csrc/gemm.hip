@@ -752,6 +752,25 @@ hipError_t launch_scale(int64_t K, int64_t M, const uint16_t* x, _Float16* xh, f
     return hipGetLastError();
 }
 
+// fp16 activations to the tiled layout as they are (zero rows fill the last
+// token tile): one 16-byte piece per thread, in the order of the copy.
+__global__ __launch_bounds__(256) void tile_copy_kernel(const _Float16* __restrict__ x, int K, int M,
+                                                        _Float16* __restrict__ xh, int pieces) {
+    const int o = static_cast<int>(blockIdx.x) * 256 + threadIdx.x;
+    if (o >= pieces) return;
+    const int slices = K >> 5, l = o & 63, sl = (o >> 6) % slices, t = (o >> 6) / slices * 16 + (l & 15);
+    uint4 v{0u, 0u, 0u, 0u};
+    if (t < M) v = *reinterpret_cast<const uint4*>(x + static_cast<size_t>(t) * K + 32 * sl + 8 * (l >> 4));
+    *reinterpret_cast<uint4*>(xh + static_cast<size_t>(o) * 8) = v;
+}
+
+hipError_t launch_tile_copy(int64_t K, int64_t M, const _Float16* x, _Float16* xh, hipStream_t s) {
+    const int pieces = static_cast<int>((M + 15) / 16 * 16 * K / 8);  // (at most 64 tokens and a buffer's 2^31 bytes)
+    hipLaunchKernelGGL(tile_copy_kernel, dim3(static_cast<unsigned>((pieces + 255) / 256)), dim3(256), 0, s, x,
+                       static_cast<int>(K), static_cast<int>(M), xh, pieces);
+    return hipGetLastError();
+}
+
 // Tiling of one product: token tiles of 64 (M <= 64) or 128 tokens, row
 // tiles of 128; when that leaves fewer than 256 workgroups the K range is
 // split (at packet boundaries) until there are about 256, and into runs of
@@ -784,11 +803,11 @@ GemmPlan plan_gemm(int64_t N, int64_t K, int64_t M) {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t{255}; }
 
-// The 16-token kernel (launch_skinny_batch); above it mid_serves decides.
+// The 16-token kernel (launch_skinny_batch); above it mid_plan decides.
 inline bool use_skinny(int64_t M) { return M <= kSkinnyMaxM; }
 
 size_t partial_bytes(int64_t N, int64_t K, int64_t M) {
-    if (M <= kSkinnyMaxM) return 0;  // the small-batch kernel needs no partials (above: either kernel, see mid_serves)
+    if (M <= kSkinnyMaxM) return 0;  // the small-batch kernel needs no partials (above: either kernel, see mid_plan)
     const GemmPlan p = plan_gemm(N, K, M);
     return p.splits > 1 ? static_cast<size_t>(p.splits) * M * N * 4 : 0;
 }
@@ -853,6 +872,11 @@ size_t gemm_workspace_bytes(int64_t N, int64_t K, int64_t M, int x_dtype) {
     return b + partial_bytes(N, K, M);
 }
 
+// The workspace of an f16 product (its fp32 partials) holds a tiled copy of x.
+static bool copy_room(int64_t N, int64_t K, int64_t M) {
+    return gemm_workspace_bytes(N, K, M, UNISVQ_F16) >= static_cast<size_t>((M + 15) / 16 * 16) * K * 2;
+}
+
 size_t gemm_var_workspace_bytes(int64_t N, int64_t K, int64_t M, int x_dtype) {
     size_t b = 0;
     if (x_dtype == UNISVQ_BF16) b += align256(static_cast<size_t>(M) * K * 2) + align256(static_cast<size_t>(M) * 4);
@@ -906,9 +930,14 @@ int gemm_common(int64_t N, int64_t K, const uint8_t* packed, const uint8_t* affi
         return launch_skinny(N, K, packed, affine, affine_one, M, xh, inv, y, y_dtype, s) == hipSuccess
                    ? UNISVQ_OK
                    : UNISVQ_EHIP;
-    if (!var && mid_serves(&N, 1, K, M, x_dtype == UNISVQ_BF16)) {
+    const MidPlan mid = var ? MidPlan{false, false} : mid_plan(&N, 1, K, M, x_dtype == UNISVQ_BF16, copy_room(N, K, M));
+    if (mid.serves) {
+        if (mid.copy && !tiled) {  // f16
+            if (launch_tile_copy(K, M, xh, reinterpret_cast<_Float16*>(ws), s) != hipSuccess) return UNISVQ_EHIP;
+            xh = reinterpret_cast<const _Float16*>(ws);
+        }
         const SkinnyProblem q{packed, affine, affine_one, xh, inv, y, N, K};
-        return launch_mid_batch(&q, 1, M, tiled, y_dtype, s) == hipSuccess ? UNISVQ_OK : UNISVQ_EHIP;
+        return launch_mid_batch(&q, 1, M, mid.copy, y_dtype, s) == hipSuccess ? UNISVQ_OK : UNISVQ_EHIP;
     }
     float* partial = reinterpret_cast<float*>(ws);
     // The activation buffer is addressed with 32-bit offsets: slice M.  The
@@ -980,7 +1009,10 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
         ns[i] = probs[i].N;
         kmax = probs[i].K > kmax ? probs[i].K : kmax;
     }
-    const bool mid = mid_serves(ns, count, kmax, M, x_dtype == UNISVQ_BF16), skinny = use_skinny(M) || mid;
+    bool room = true;
+    for (int i = 0; i < count; ++i) room = room && copy_room(probs[i].N, probs[i].K, M);
+    const MidPlan mid = mid_plan(ns, count, kmax, M, x_dtype == UNISVQ_BF16, room);
+    const bool skinny = use_skinny(M) || mid.serves;
     if (!skinny && sliced) {
         // activations above 2 GiB: one product at a time, in token slices
         for (int i = 0; i < count; ++i) {
@@ -1062,12 +1094,13 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
         if (st != UNISVQ_EUNSUP) return st;  // else K too long for its LDS: the small-batch kernel
     }
     // small batches, one launch; bf16 activations as their scaled fp16 copy
-    // (row-major up to 16 tokens, tiled above)
+    // (row-major up to 16 tokens, tiled above),
+    // f16 ones as a tiled copy where mid_plan says so
     SkinnyProblem sp[kMaxBatch];
     for (int i = 0; i < count; ++i) {
         const GemmBatchProblem& q = probs[i];
         sp[i] = SkinnyProblem{q.packed, nullptr, 0, static_cast<const _Float16*>(q.x), nullptr, q.y, q.N, q.K};
-        if (x_dtype == UNISVQ_BF16) {
+        if (x_dtype == UNISVQ_BF16 || mid.copy) {
             // the problem's own copy, or that of an earlier problem with the
             // same activations (one copy keeps them shared, so that workgroups
             // of the 16-token kernel may span the problems)
@@ -1078,21 +1111,23 @@ int launch_gemm_batch(const GemmBatchProblem* probs, int count, int64_t M, int x
                 sp[i].x = sp[same].x;
                 sp[i].inv_scale = sp[same].inv_scale;
             } else {
-                const int64_t mx = mid ? (M + 15) / 16 * 16 : M;
+                const int64_t mx = mid.copy ? (M + 15) / 16 * 16 : M;
                 _Float16* wxh = reinterpret_cast<_Float16*>(ws);
                 float* winv = reinterpret_cast<float*>(ws + align256(static_cast<size_t>(mx) * q.K * 2));
                 const uint16_t* xb = static_cast<const uint16_t*>(q.x);
-                if ((mid ? launch_scale<true>(q.K, M, xb, wxh, winv, s) : launch_scale<false>(q.K, M, xb, wxh, winv, s)) !=
-                    hipSuccess)
-                    return q.K > 65536 ? UNISVQ_EUNSUP : UNISVQ_EHIP;
+                hipError_t e;
+                if (x_dtype != UNISVQ_BF16) e = launch_tile_copy(q.K, M, sp[i].x, wxh, s);
+                else if (mid.copy) e = launch_scale<true>(q.K, M, xb, wxh, winv, s);
+                else e = launch_scale<false>(q.K, M, xb, wxh, winv, s);
+                if (e != hipSuccess) return q.K > 65536 && x_dtype == UNISVQ_BF16 ? UNISVQ_EUNSUP : UNISVQ_EHIP;
                 sp[i].x = wxh;
-                sp[i].inv_scale = winv;
+                sp[i].inv_scale = x_dtype == UNISVQ_BF16 ? winv : nullptr;
             }
         }
         ws += align256(gemm_workspace_bytes(q.N, q.K, M, x_dtype));
     }
-    const hipError_t e = mid ? launch_mid_batch(sp, count, M, x_dtype == UNISVQ_BF16, y_dtype, s)
-                             : launch_skinny_batch(sp, count, M, y_dtype, s);
+    const hipError_t e = mid.serves ? launch_mid_batch(sp, count, M, mid.copy, y_dtype, s)
+                                    : launch_skinny_batch(sp, count, M, y_dtype, s);
     return e == hipSuccess ? UNISVQ_OK : UNISVQ_EHIP;
 }
 

@@ -43,28 +43,31 @@ int mid_height(const int64_t* N, int count, int64_t K, int64_t M, int64_t& round
 }  // namespace
 
 // Against the tiled product with its K split, partial sums and second launch
-// (us, this kernel against that one; each with its bf16 pre-pass where there
-// is one):
-//  * up to 32 tokens always: 7B layer o 8.8 / 14.8 (17 tokens), 11.5 / 15.7
-//    (32), q+k+v 16.6 / 25.2, gate+up 23.1 / 37.6, down 25.5 / 25.6 (32), 70B
-//    gate+up 108 / 112, down 64 / 75 (32);
-//  * tiled activations to 64 tokens, unless the batch has the 32768 rows from
-//    which the tiled product no longer splits K: 64 tokens o 17 / 24, gate+up 38
-//    / 47, 70B down 98 / 110, but 70B gate+up (57344 rows) 141 / 122;
-//  * row-major activations above 32 tokens, read in pieces of 64 bytes by every
-//    workgroup, while a CU's share is small: rounds * M * K below 2^18 (48
-//    tokens, K = 4096: o 15.5 / 17.1, gate+up 28.3 / 39.2; at 64 tokens o 19.7 /
-//    18.2, gate+up 44.8 / 40.9; 48 tokens, K = 11008 36 / 26; 64 tokens, K = 2048,
-//    11264 rows 15.4 / 21.3).
-bool mid_serves(const int64_t* N, int count, int64_t K, int64_t M, bool tiled) {
-    if (M <= kSkinnyMaxM || M > kMidMaxM) return false;
-    if ((M + 15) / 16 * 16 * K * 2 > kMaxBufferBytes) return false;  // (32-bit offsets: the tiled product slices)
-    if (M <= 32) return true;
+// (us, this kernel against that one):
+//  * up to 32 tokens always: 7B layer, f16, o 8.8 / 14.8 (17 tokens), 11.5 / 15.7
+//    (32), q+k+v 16.6 / 25.2, gate+up 23.1 / 37.6, 70B gate+up 108 / 112, down 64
+//    / 75 (32);
+//  * to 64 tokens from the tiled layout, unless the batch has the 32768 rows from
+//    which the tiled product no longer splits K: bf16, 64 tokens, o 17 / 24,
+//    gate+up 38 / 47, 70B down 98 / 110, but 70B gate+up (57344 rows) 141 / 122;
+//  * to 64 tokens from row-major activations while a CU's share of them, rounds *
+//    M * K, is below 2^18 (48 tokens: gate+up 28.3 / 39.2; K = 11008 36 / 26; 64
+//    tokens: K = 2048, 11264 rows 15.4 / 21.3, o 19.7 / 18.2).
+// Every workgroup reads all activations, row-major ones in pieces of 64 bytes at
+// 15 bytes a clock and CU, the tiled layout at more than twice that, so above a
+// share of 3 * 2^16 (2^18 up to 32 tokens) a copy into it (a launch of about 2
+// us) pays: f16, copied against row-major, 64 tokens: o 12.7 / 19.7, q+k+v 21.4 /
+// 25.3, gate+up 33.6 / 44.8 (and 18.2, 27.2, 40.9 on the tiled product); 24
+// tokens: K = 11008 17.4 / 21.3, but K = 8192 (a share of 3 * 2^16) 23.7 / 21.1.
+MidPlan mid_plan(const int64_t* N, int count, int64_t K, int64_t M, bool bf16, bool room) {
+    if (M <= kSkinnyMaxM || M > kMidMaxM) return {false, false};
+    if ((M + 15) / 16 * 16 * K * 2 > kMaxBufferBytes) return {false, false};  // (32-bit offsets: the tiled product slices)
     int64_t rows = 0, rounds = 1;
     for (int i = 0; i < count; ++i) rows += N[i];
-    if (tiled) return rows < 32768;
     mid_height(N, count, K, M, rounds);
-    return rounds * M * K < (1 << 18);
+    const int64_t share = rounds * M * K;
+    const bool copy = bf16 || (room && share >= (M <= 32 ? 1 << 18 : 3 << 16));
+    return {M <= 32 || (copy ? rows < 32768 : share < (1 << 18)), copy};
 }
 
 hipError_t launch_mid_batch(const SkinnyProblem* probs, int count, int64_t M, bool tiled, int y_dtype, hipStream_t s) {

@@ -386,7 +386,7 @@ def bench_ldlq(args):
         "weight_mse": {"ldlq": round(mse(E_l), 5), "nearest": round(mse(E_r), 5)},
         "roofline": {"bound": "alu", "achieved": round(ach, 2), "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(ach / PEAK_FP64_TFLOPS, 4), "traffic": None,
-                     "kernel": "ldlq_block_kernel + ldlq_update_kernel", "avg_launch_us": None},
+                     "kernel": "ldlq_kernel", "avg_launch_us": None},
         "cpu_baseline": cpu,
     }
     print(json.dumps(out), flush=True)
@@ -677,12 +677,14 @@ def product_kernel_name(case):
     if not case.ws.var and not case.fold and case.M <= SKINNY_MAX_M:
         return "skinny_kernel"
     if not case.ws.var and not case.fold and case.M <= 32:
-        return "skinny_kernel or gemm_kernel (by launch width)"
+        return "mid_kernel"
+    if not case.ws.var and not case.fold and case.M <= 64:
+        return "mid_kernel or gemm_kernel (by launch width)"
     return "gemm_kernel"
 
 
-# Largest batch the 2x4 product always sends to the small-batch kernel (from
-# 17 to 32 tokens only launches of fewer than 64 tiles of 128 rows go there).
+# Largest batch of the 2x4 product on the small-batch kernel (to 32 tokens the
+# mid-batch kernel follows, to 64 that or the tiled product).
 SKINNY_MAX_M = 16
 
 

@@ -23,9 +23,9 @@
 //     factorises it pivot block by pivot block while the others update
 //     theirs (the panel's serial part: as a launch of its own it was 1.4 of
 //     3.1 ms at K = 4096).
-// K = 4096, MI355X: 1.84 ms (3.14 before).  A diagonal block alone takes 12 us
+// K = 4096, MI355X: 1.9 ms (3.14 before).  A diagonal block alone takes 14 us
 // (23 with its 64 x 64 block in LDS and two barriers per pivot); a trailing
-// launch 45 to 15 us, the lower end set by the pivots; a strip 5 to 8 us.
+// launch 42 to 17 us, the lower end set by the pivots; a strip 5 to 8 us.
 // Error against an 80-bit factorisation (K = 128 to 1024, twelve Hessians of
 // condition about 1e5): 9e-15 to 1.1e-13, as before.
 // Every pivot block is checked for positive definiteness (its leading

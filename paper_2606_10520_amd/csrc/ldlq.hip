@@ -54,6 +54,7 @@ constexpr int kFarRows = 128;            // far workgroup: 128 rows x 64 columns
 constexpr int kFarCols = 64;
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef f64x4 f64x4m __attribute__((aligned(16)));  // in the workspace, which is 16-byte aligned
 
 __device__ inline double h2d(uint16_t h) {
     return static_cast<double>(static_cast<float>(__builtin_bit_cast(_Float16, h)));
@@ -425,7 +426,7 @@ __device__ inline void ldlq_step(StepLds& sh, int64_t K, int b, int64_t rb, cons
         if (b >= 2) {
 #pragma unroll
             for (int q = 0; q < 2; ++q)
-                acc[q] = *reinterpret_cast<const f64x4*>(blk + (4 * h + q0 + q) * 256 + 4 * lane);
+                acc[q] = *reinterpret_cast<const f64x4m*>(blk + (4 * h + q0 + q) * 256 + 4 * lane);
         }
         if (b >= 1) {
             const double* ep = blk - kBlkDoubles + 2 * lane;
@@ -578,7 +579,7 @@ __device__ inline void ldlq_far(int64_t N, int64_t K, int b, int64_t rb0, int64_
     const bool first = kb0 == 0;  // the first errors that this column block gets: F starts at zero
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const f64x4 v0 = *reinterpret_cast<const f64x4*>(f0 + 256 * q), v1 = *reinterpret_cast<const f64x4*>(f1 + 256 * q);
+        const f64x4 v0 = *reinterpret_cast<const f64x4m*>(f0 + 256 * q), v1 = *reinterpret_cast<const f64x4m*>(f1 + 256 * q);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             acc[0][q][i] = first ? 0.0 : v0[i];
@@ -596,8 +597,8 @@ __device__ inline void ldlq_far(int64_t N, int64_t K, int b, int64_t rb0, int64_
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        *reinterpret_cast<f64x4*>(f0 + 256 * q) = acc[0][q];
-        *reinterpret_cast<f64x4*>(f1 + 256 * q) = acc[1][q];
+        *reinterpret_cast<f64x4m*>(f0 + 256 * q) = acc[0][q];
+        *reinterpret_cast<f64x4m*>(f1 + 256 * q) = acc[1][q];
     }
 }
 

@@ -63,3 +63,20 @@ def test_magnitudes(a, w):
     B = (rng.uniform(-1, 1, (N, K // 128, 4)) * a).astype(np.float16)
     U, _ = oracle.ldl_blocks(hessian(rng, K))
     check(W, U, A, B, 0)
+
+
+def test_workspace_at_16_bytes():
+    """A workspace aligned to 16 bytes and no more, with stale NaNs in it."""
+    import paper_2606_10520_amd.unisvq as u
+    from test_gpu_ldlq import DEV, dev_half
+    rng = np.random.default_rng(21)
+    N, K = 48, 640
+    W = rng.standard_normal((N, K)).astype(np.float32)
+    A, B, ga = pairs(rng, N, K, "row_group")
+    U, _ = oracle.ldl_blocks(hessian(rng, K))
+    buf = torch.full((u.ldlq_workspace_bytes(N, K) // 8 + 64,), float("nan"), dtype=torch.float64, device=DEV)
+    off = (16 - buf.data_ptr()) % 32 // 8  # doubles to an address of 16 modulo 32
+    got = u.ldlq(torch.from_numpy(W).to(DEV), torch.from_numpy(U).to(DEV), dev_half(A), dev_half(B), ga,
+                 workspace=buf[off:].view(torch.uint8))
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.ldlq(W, U, A, B, shared=False)[0])

@@ -138,7 +138,8 @@ struct DecOps {
 // Per-lane constants of the gathers (j = lane % 4).
 struct DecLane {
     uint32_t rot4, keep4, rot2, keep2;  // code transpose: rotations and kept fields of its two stages
-    f16x4 unit;                         // 1 at element j
+    uint32_t keep_a, send_a;            // A transpose: halves kept and sent in its second stage
+    bool low, even;                     // j < 2, j even
 };
 
 __device__ inline DecLane make_dec_lane(int j) {
@@ -147,8 +148,12 @@ __device__ inline DecLane make_dec_lane(int j) {
     l.keep4 = j < 2 ? 0x0f0f0f0fu : 0xf0f0f0f0u;
     l.rot2 = (j & 1) == 0 ? 30u : 2u;
     l.keep2 = (j & 1) == 0 ? 0x33333333u : 0xccccccccu;
-    const _Float16 one = static_cast<_Float16>(1.0f), zero = static_cast<_Float16>(0.0f);
-    l.unit = f16x4{j == 0 ? one : zero, j == 1 ? one : zero, j == 2 ? one : zero, j == 3 ? one : zero};
+    l.low = j < 2;
+    l.even = (j & 1) == 0;
+    // lower or upper halves of (own, received) word, the lower column first
+    const uint32_t lo = l.low ? 0x05040100u : 0x01000504u, hi = l.low ? 0x07060302u : 0x03020706u;
+    l.keep_a = l.even ? lo : hi;
+    l.send_a = l.even ? hi : lo;
     return l;
 }
 
@@ -179,15 +184,20 @@ __device__ inline uint32_t transpose_fields(uint32_t w, const DecLane& l) {
 //   Codes: lane b's word holds component b's 2-bit codes, field k of each
 //   byte for vector 4(byte) + k; lane j needs field j of every lane's word:
 //   the transpose above, then two masks.
-//   A: lane b holds column b, lane j needs row j: one 4x4x4 instruction with
-//   the unit matrix (block = row: D[i][n] = sum_k A[k][i] I[k][n], lane n gets
-//   A[n][0..3]), exact in fp32 and exact back in fp16.
-//   B: lane b holds B[b], each lane needs all four: the same with the unit
-//   vector of k = 0.
-// 21 vector instructions and two 4x4x4 for a tile; gathering codes, A and B
+//   A: lane b holds column b (rows 0, 1 in word al, rows 2, 3 in ah), lane j
+//   needs row j: a 4 x 4 transpose of 16-bit elements in two stages, across
+//   lanes j ^ 2 (words) and j ^ 1 (halves), eight instructions.  Bits are only
+//   moved: a product with the unit matrix is one instruction and two
+//   conversions, but turns an infinite entry into NaNs in the other rows of its
+//   column (inf * 0).
+//   B: lane b holds B[b], each lane needs all four: one 4x4x4 instruction, whose
+//   only non-zero second operand is 1 at k = 0 (lane b's value times 1, the other
+//   terms 0 * 0: exact, infinities and subnormals included).
+// 27 vector instructions and one 4x4x4 for a tile; gathering codes, A and B
 // lane by lane took 40, of the 84 issue slots that bound the kernels that
-// decode (7B layer, 16 tokens: 50.4 -> 48.2 us; prefill at 2048 tokens: 999 ->
-// 967 us).
+// decode (7B layer, 16 tokens: 50.4 -> 48.7 us, of which A's transpose by
+// instructions instead of the unit matrix costs 0.5; prefill at 2048 tokens:
+// 999 -> 967 us with either).
 // CODES_ONLY (the Eq. 9 fold, where A and B act on the activations): the
 // codes alone.
 template <bool CODES_ONLY = false>
@@ -199,14 +209,16 @@ __device__ inline void prepare(const Piece& pc, const DecLane& l, int jj, DecOps
         d.o[h] = (cw[h] >> 2) & 0x33333333u;
     }
     if constexpr (CODES_ONLY) return;
+    const uint32_t al = jj ? pc.a.z : pc.a.x, ah = jj ? pc.a.w : pc.a.y;
+    const uint32_t own = l.low ? al : ah;                    // rows 2 (j / 2), + 1 of column j
+    const uint32_t got = quad_perm<0x4e>(l.low ? ah : al);  // and of column j ^ 2
+    const uint32_t kept = __builtin_amdgcn_perm(got, own, l.keep_a);                   // row j: columns j % 2, + 2
+    const uint32_t sent = quad_perm<0xb1>(__builtin_amdgcn_perm(got, own, l.send_a));  // and the other two
+    d.arow = __builtin_bit_cast(f16x4, l.even ? uint2{kept, sent} : uint2{sent, kept});
     const _Float16 one = static_cast<_Float16>(1.0f), zero = static_cast<_Float16>(0.0f);
-    const f16x4 acol = __builtin_bit_cast(f16x4, jj ? uint2{pc.a.z, pc.a.w} : uint2{pc.a.x, pc.a.y});
     const f16x4 bcol = __builtin_bit_cast(f16x4, uint2{jj ? pc.b >> 16 : pc.b & 0xffffu, 0u});
     const f32x4 none = {0.f, 0.f, 0.f, 0.f};
-    const f32x4 row = __builtin_amdgcn_mfma_f32_4x4x4f16(acol, l.unit, none, 0, 0, 0);
     d.bvec = __builtin_amdgcn_mfma_f32_4x4x4f16(bcol, f16x4{one, zero, zero, zero}, none, 0, 0, 0);
-    d.arow = f16x4{static_cast<_Float16>(row[0]), static_cast<_Float16>(row[2]), static_cast<_Float16>(row[1]),
-                   static_cast<_Float16>(row[3])};
 }
 
 // Vectors 4N .. 4N+3 of the row block: one matrix-core instruction; lane

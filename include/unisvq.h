@@ -212,7 +212,9 @@ int unisvq_gemv_batched(const unisvq_gemv_problem* problems, int count, int64_t 
  * up to a multiple of 16) and one fp32 scale per token (rounded up to 256);
  * above 16 tokens, for products with too few output tiles to fill the GPU,
  * fp32 partial sums of a split along K (splits*M*N*4 bytes).  From 17 to 64
- * tokens the size covers either kernel below (the one taken may use less).
+ * tokens the size covers either kernel below (the one taken may use less), and
+ * f16 products may use the partial sums' part for a copy of x in 16-token tiles
+ * where it is large enough.
  * 0 also for an invalid shape, M < 1 or an unknown x_dtype.  Host-only, no GPU needed. */
 size_t unisvq_gemm_workspace_bytes(int64_t N, int64_t K, int64_t M, int x_dtype);
 
@@ -220,14 +222,17 @@ size_t unisvq_gemm_workspace_bytes(int64_t N, int64_t K, int64_t M, int x_dtype)
  * Arguments as unisvq_gemv; x_dtype F16 or BF16, y_dtype F16, BF16 or F32.
  * Up to 3 tokens the matrix-vector kernel of unisvq_gemv computes it (its
  * faster range; the workspace then goes unused), unless K is too long for
- * that kernel's LDS.  Up to 32 tokens -- and up to 64 where measured faster:
- * bf16 activations and fewer than 32768 rows, or f16 activations and a small
- * M*K per compute unit -- one launch of a small-batch kernel computes it: each
- * wavefront decodes 16-row x 128-column tiles into its own LDS region and
- * multiplies them with all tokens at once; the wavefronts of a workgroup
- * split K and add their sums in a fixed order (no workspace beyond the bf16
- * copy below).  Otherwise each
- * workgroup decodes a 128-row x 128-column weight tile at a time into
+ * that kernel's LDS.  Up to 16 tokens, and up to 64 where that measured faster,
+ * one launch of a small-batch kernel computes it: each wavefront decodes
+ * 16-row x 128-column tiles into its own LDS region and multiplies them with
+ * all tokens at once; the wavefronts of a workgroup split K and add their sums
+ * in a fixed order, so there are no partial sums in the workspace.  From 17 to
+ * 32 tokens that is every product of fewer than 32768 rows and K >= 512, and
+ * wider ones as far as K is long enough; from 33 to 64 tokens those of fewer
+ * than 32768 rows but not of few rows for their M*K (512 rows at K = 8192, 4096
+ * at K = 28672).  There bf16 activations go through the copy below, and f16 ones
+ * are copied to 16-token tiles in the workspace where M*K is large and it has
+ * the room (same results either way).  Otherwise each workgroup decodes a 128-row x 128-column weight tile at a time into
  * LDS (every vector A q + B in fp32 from the exact integer codes, rounded
  * once to fp16) and multiplies it with its tokens on the matrix cores
  * (fp16 x fp16, fp32 accumulation); decoded weights never reach global
@@ -257,14 +262,17 @@ size_t unisvq_gemm_batched_workspace_bytes(const unisvq_gemv_problem* problems, 
  * projections, at a small batch).  For M <= 16 all of them run in ONE launch
  * (of the matrix-vector kernel up to 3 tokens, as unisvq_gemm does, else of
  * the small-batch kernel), with the results of unisvq_gemm on each bit for
- * bit; so also from 17 to 32 tokens, and to 64 where unisvq_gemm's rule, applied
- * to the whole batch, takes the small-batch kernel; otherwise in ONE launch of the tiled product, planned over the whole
- * batch, plus one reduction launch when the batch's tiles leave CUs idle and
- * K is split -- the same arithmetic as unisvq_gemm, but the K split (and so
- * the grouping of the fp32 partial sums) follows the batch, so results can
- * differ from single calls in the last bits (bf16 activations first pass
- * through the pre-pass, once per distinct buffer, into the workspace; activations
- * above 2 GiB fall back to one product at a time, as single calls).
+ * bit.  From 17 to 64 tokens unisvq_gemm's rule, applied to all the batch's rows
+ * and its longest K, decides whether they run in ONE launch of the small-batch
+ * kernel; a problem whose single call takes that kernel too has the same
+ * result bit for bit (to 32 tokens: every batch of fewer than 32768 rows and K
+ * >= 512).  Otherwise they run in ONE launch of the tiled product, planned over
+ * the whole batch, plus one reduction launch when the batch's tiles leave CUs
+ * idle and K is split -- the same arithmetic as unisvq_gemm, but the K split
+ * (and so the grouping of the fp32 partial sums) follows the batch, so results
+ * can differ from single calls in the last bits.  Activations are copied (bf16
+ * ones always, f16 ones as in unisvq_gemm) once per distinct buffer and K;
+ * activations above 2 GiB fall back to one product at a time, as single calls.
  *   problems   HOST array of `count` descriptors (1..UNISVQ_MAX_BATCH), read
  *              before the call returns; packed format v1 weights; every
  *              descriptor is validated before anything is enqueued
@@ -470,9 +478,11 @@ int unisvq_quantize(int64_t N, int64_t K, const float* W, const uint16_t* A, con
  *              0: per (row, group); 1 or K/128: row-shared)
  *   codes      device uint8 [N][K] (0..3), 4-byte aligned
  *   workspace  device, >= unisvq_ldlq_workspace_bytes(N, K) bytes (fp64 running
- *              feedback and one block of errors), 16-byte aligned; overwritten
- * Work: K/128 pairs of launches (each block of 128 columns: rounding with
- * in-block feedback, then the feedback to every later column). */
+ *              feedback, in whose place each block's errors go), 16-byte
+ *              aligned; overwritten
+ * Work: K/128 launches, one for each block of 128 columns: its rounding with
+ * in-block feedback, and beside it the feedback of the two blocks before it
+ * to every other later block. */
 size_t unisvq_ldlq_workspace_bytes(int64_t N, int64_t K);
 int unisvq_ldlq(int64_t N, int64_t K, const float* W, const double* U, const uint16_t* A, const uint16_t* B,
                 int64_t affine_groups, uint8_t* codes, void* workspace, size_t workspace_bytes, void* stream);
@@ -500,7 +510,8 @@ int unisvq_ldlq(int64_t N, int64_t K, const float* W, const double* U, const uin
  *              are asynchronous: read it after synchronising the stream.
  *   workspace  device, >= unisvq_ldl_workspace_bytes(K) bytes (K x 64 fp64 and
  *              the panel's pivot inverses), 16-byte aligned; overwritten
- * Work: one set-up launch and 3 K/64 - 2 launches of the panel steps.
+ * Work: one set-up launch, one for the last panel's diagonal block and two for
+ * every other panel: 2 K/64 in all.
  * unisvq_ldl_workspace_bytes returns 0 for a K outside the range above. */
 size_t unisvq_ldl_workspace_bytes(int64_t K);
 int unisvq_ldl(int64_t K, const double* H, double* U, double* D, int32_t* info, void* workspace,

@@ -227,7 +227,8 @@ MidPlan mid_plan(const int64_t* N, int count, int64_t K, int64_t M, bool bf16, b
 hipError_t launch_mid_batch(const SkinnyProblem* probs, int count, int64_t M, bool tiled, int y_dtype, hipStream_t s);
 // unisvq_gemm over a batch of problems (same M and dtypes): one launch of the
 // small-batch kernels where they serve the batch, else one tiled launch (and one
-// reduction) for the batch, after the bf16 pre-passes.
+// reduction) for the batch, after the copies of the activations (bf16 always,
+// f16 for the kernel of 17 to 64 tokens as mid_plan says).
 // Problem i uses the workspace bytes [off_i, off_i + gemm_workspace_bytes(i)),
 // off_i the 256-aligned sum of the earlier ones (gemm_batch_workspace_bytes).
 struct GemmBatchProblem {

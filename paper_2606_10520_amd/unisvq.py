@@ -417,7 +417,8 @@ def gemm_noalloc(packed, N: int, K: int, x, out=None, out_dtype=None, stream=Non
 
 def gemm_batched(problems, out_dtype=None, workspace=None, stream=None):
     """Several independent products (same M and dtypes), each as unisvq_gemm:
-    one launch (plus one reduction launch above 32 tokens when K is split).
+    one launch (plus one for each distinct activation buffer that is copied
+    first, and one reduction launch when K is split).
     problems: sequence of (packed, N, K, x, out-or-None).
     Returns the list of outputs."""
     if not 1 <= len(problems) <= MAX_BATCH:

@@ -736,12 +736,12 @@ def test_read_bytes_folds_every_word():
 def test_gemm_batched_matches_single_calls(M, dtype):
     """q/k/v-style and gate/up-style batches (different N and K in one
     launch, an odd group count), every output element against the oracle.
-    Up to 32 tokens this batch (45 tiles of 128 rows, as each of its problems
-    alone) runs on the small-batch kernel, and each output equals unisvq_gemm
-    on that problem alone bit for bit (the same kernel, workgroup and
-    summation order); above, the batch plans its own K split, so the outputs
-    equal single calls to within the fp32 regrouping of the partial sums, and
-    repeat bit for bit."""
+    Up to 32 tokens this batch, as each of its problems alone, runs on a
+    small-batch kernel, and each output equals unisvq_gemm on that problem
+    alone bit for bit (the same summation order); above, batch and single call
+    may take different kernels (to 64 tokens) or K splits, so the outputs equal
+    single calls to within the fp32 regrouping of the sums, and repeat bit for
+    bit."""
     shapes = [(4096, 4096), (1024, 4096), (512, 11008), (64, 1152)]
     probs, refs = [], []
     for i, (N, K) in enumerate(shapes):
@@ -768,11 +768,10 @@ def test_gemm_batched_matches_single_calls(M, dtype):
 @pytest.mark.parametrize("M", [17, 24, 32])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_gemm_batched_wide_batch_above_16_tokens(M, dtype):
-    """From 17 to 32 tokens a batch of 64 or more tiles of 128 rows (here the
-    7B q+k+v shape, 96 tiles) runs on the tiled product while each problem
-    alone (32 tiles) stays on the small-batch kernel: both against the oracle
-    over every element, and against each other within the fp32 regrouping of
-    their sums."""
+    """From 17 to 32 tokens a wide batch (here the 7B q+k+v shape on one
+    activation buffer) and each of its problems alone run on the kernel of 17 to
+    64 tokens, at different workgroup heights but in the same summation order:
+    both against the oracle over every element, and equal bit for bit."""
     N, K = 4096, 4096
     xb = wl.gen_activations(M, K, seed=141, dtype=dtype, outliers=True)
     x = dev_x(xb, dtype)
@@ -790,7 +789,7 @@ def test_gemm_batched_wide_batch_above_16_tokens(M, dtype):
         assert torch.equal(y, y2)
         assert rel_err(y.cpu().numpy(), ref) <= 5e-4
         assert rel_err(single.cpu().numpy(), ref) <= 5e-4
-        assert rel_err(y.cpu().numpy(), single.cpu().numpy().astype(np.float64)) <= 1e-5
+        assert torch.equal(y, single)
 
 
 SPAN_SETS = {
@@ -845,8 +844,8 @@ def test_gemm_batched_fp16_outputs_and_reruns():
 
 
 # Small-batch launches by workgroup height (the launcher's choice for these
-# batches at up to 16 tokens; above 16 tokens every workgroup has one row
-# block): six row blocks per workgroup (two 11008-row problems, 230
+# batches at up to 16 tokens; above, the kernel of 17 to 64 tokens chooses its
+# own): six row blocks per workgroup (two 11008-row problems, 230
 # workgroups, the last of each with four), four (1024 row blocks), three
 # (a 70B-q+k+v-like batch, 215 workgroups, the last of the first problem with
 # two row blocks), three again for a mix with multi-packet wavefronts, two (4112 rows: 129

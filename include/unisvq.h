@@ -477,9 +477,10 @@ int unisvq_quantize(int64_t N, int64_t K, const float* W, const uint16_t* A, con
  *   A, B       device fp16 bits, pair layouts as unisvq_quantize (affine_groups
  *              0: per (row, group); 1 or K/128: row-shared)
  *   codes      device uint8 [N][K] (0..3), 4-byte aligned
- *   workspace  device, >= unisvq_ldlq_workspace_bytes(N, K) bytes (fp64 running
- *              feedback, in whose place each block's errors go), 16-byte
- *              aligned; overwritten
+ *   workspace  device, >= unisvq_ldlq_workspace_bytes(N, K) bytes (N*K*8 for the
+ *              fp64 running feedback, in whose place each block's errors go,
+ *              and N*128*8 that are unused at present), 16-byte aligned;
+ *              overwritten
  * Work: K/128 launches, one for each block of 128 columns: its rounding with
  * in-block feedback, and beside it the feedback of the two blocks before it
  * to every other later block. */

@@ -624,8 +624,9 @@ __global__ __launch_bounds__(256, 2) void ldlq_kernel(int64_t N, int64_t K, int 
 
 }  // namespace
 
-// (F and E share one N x K area; the rest of the size is kept for callers
-// that sized their workspace before)
+// F and E share one N x K area.  The N x 128 doubles beyond it are not touched:
+// they are part of the size that the interface has stated since E had an area
+// of its own, and a buffer without them stays refused.
 size_t ldlq_workspace_bytes(int64_t N, int64_t K) {
     return static_cast<size_t>(N) * static_cast<size_t>(K) * 8 + static_cast<size_t>(N) * kLdlqBlock * 8;
 }

@@ -221,6 +221,14 @@ __device__ inline void prepare(const Piece& pc, const DecLane& l, int jj, DecOps
     d.bvec = __builtin_amdgcn_mfma_f32_4x4x4f16(bcol, f16x4{one, zero, zero, zero}, none, 0, 0, 0);
 }
 
+// fp32 weights of one vector -> fp16 (one rounding), stored at dst.
+__device__ inline void store_w4(const f32x4& w, _Float16* dst) {
+    f16x4 o;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) o[a] = static_cast<_Float16>(w[a]);
+    *reinterpret_cast<f16x4*>(dst) = o;
+}
+
 // Vectors 4N .. 4N+3 of the row block: one matrix-core instruction; lane
 // (beta, j) gets vector 4N+j, which decode_vecs stores at dst + 16N + 4j (dst =
 // the lane's row).  CODES_ONLY: the four codes themselves (exact small
@@ -240,11 +248,7 @@ __device__ inline void decode_vecs(const DecOps& d, _Float16* dst, int j) {
         *reinterpret_cast<f16x4*>(dst + 16 * N + 4 * j) = q;
         return;
     }
-    const f32x4 w = __builtin_amdgcn_mfma_f32_4x4x4f16(d.arow, q, d.bvec, 0, 0, 0);
-    f16x4 o;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) o[a] = static_cast<_Float16>(w[a]);
-    *reinterpret_cast<f16x4*>(dst + 16 * N + 4 * j) = o;
+    store_w4(__builtin_amdgcn_mfma_f32_4x4x4f16(d.arow, q, d.bvec, 0, 0, 0), dst + 16 * N + 4 * j);
 }
 
 // Half H of a tile (vectors 16 H .. 16 H + 15 of every row), in fp32: four
@@ -254,14 +258,6 @@ __device__ inline void decode_half(const DecOps& d, f32x4 (&w)[4]) {
     const f16x4 q[4] = {code_quad<4 * H>(d), code_quad<4 * H + 1>(d), code_quad<4 * H + 2>(d), code_quad<4 * H + 3>(d)};
 #pragma unroll
     for (int n = 0; n < 4; ++n) w[n] = __builtin_amdgcn_mfma_f32_4x4x4f16(d.arow, q[n], d.bvec, 0, 0, 0);
-}
-
-// fp32 weights of one vector -> fp16 (one rounding), stored at dst.
-__device__ inline void store_vec(const f32x4& w, void* dst) {
-    f16x4 o;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) o[a] = static_cast<_Float16>(w[a]);
-    *static_cast<f16x4*>(dst) = o;
 }
 
 }  // namespace
@@ -373,13 +369,6 @@ __device__ inline f16x4 var_codes(const uint32_t (&p01)[2], const uint32_t (&p23
     const f16x2 lo = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(p01[H], scale, NB);
     const f16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(p23[H], scale, NB);
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
-}
-
-__device__ inline void store_w4(const f32x4& w, _Float16* dst) {
-    f16x4 o;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) o[a] = static_cast<_Float16>(w[a]);
-    *reinterpret_cast<f16x4*>(dst) = o;
 }
 
 // d = 4: vectors 4N .. 4N+3; lane (beta, j) stores vector 4N+j at dst + 16N + 4j.

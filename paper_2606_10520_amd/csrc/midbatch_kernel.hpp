@@ -122,9 +122,9 @@ __global__ __launch_bounds__(WV * 64, WV / 4) void mid_kernel(const MidBatch bat
                 decode_half<0>(ops, w0);
                 decode_half<1>(ops, w1);
 #pragma unroll
-                for (int n = 0; n < 4; ++n) store_vec(w0[n], wrow + 16 * n + 4 * j);
+                for (int n = 0; n < 4; ++n) store_w4(w0[n], wrow + 16 * n + 4 * j);
 #pragma unroll
-                for (int n = 0; n < 4; ++n) store_vec(w1[n], wrow + 16 * (4 + n) + 4 * j);
+                for (int n = 0; n < 4; ++n) store_w4(w1[n], wrow + 16 * (4 + n) + 4 * j);
                 if (jj == 1) load(p + WV, b, pc[b]);
                 f16x8 wb[4];
 #pragma unroll

@@ -118,10 +118,10 @@ __device__ inline void piece_product(const Piece& pc, const DecLane& dl, int j, 
         decode_half<1>(ops[jj], w1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int n = 0; n < 4; ++n) store_vec(w0[n], wrow + 16 * n + 4 * j);
+        for (int n = 0; n < 4; ++n) store_w4(w0[n], wrow + 16 * n + 4 * j);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int n = 0; n < 4; ++n) store_vec(w1[n], wrow + 16 * (4 + n) + 4 * j);
+        for (int n = 0; n < 4; ++n) store_w4(w1[n], wrow + 16 * (4 + n) + 4 * j);
         __builtin_amdgcn_sched_barrier(0);
         tile_multiply(wlane, jj ? x1 : x0, acc);
     }

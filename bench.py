@@ -679,7 +679,7 @@ def product_kernel_name(case):
     if not case.ws.var and not case.fold and case.M <= 32:
         return "mid_kernel"
     if not case.ws.var and not case.fold and case.M <= 64:
-        return "mid_kernel or gemm_kernel (by launch width)"
+        return "mid_kernel or gemm_kernel (by launch shape)"
     return "gemm_kernel"
 
 

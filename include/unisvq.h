@@ -227,10 +227,10 @@ size_t unisvq_gemm_workspace_bytes(int64_t N, int64_t K, int64_t M, int x_dtype)
  * 16-row x 128-column tiles into its own LDS region and multiplies them with
  * all tokens at once; the wavefronts of a workgroup split K and add their sums
  * in a fixed order, so there are no partial sums in the workspace.  From 17 to
- * 32 tokens that is every product of fewer than 32768 rows and K >= 512, and
- * wider ones as far as K is long enough; from 33 to 64 tokens those of fewer
- * than 32768 rows but not of few rows for their M*K (512 rows at K = 8192, 4096
- * at K = 28672).  There bf16 activations go through the copy below, and f16 ones
+ * 32 tokens that is every product of fewer than 32768 rows and K >= 512, wider
+ * ones as far as K is long enough, and narrower ones of shorter K; from 33 to 64
+ * tokens those of fewer than 32768 rows but not of few rows for their M*K (512
+ * rows at K = 8192, 4096 at K = 28672).  There bf16 activations go through the copy below, and f16 ones
  * are copied to 16-token tiles in the workspace where M*K is large and it has
  * the room (same results either way).  Otherwise each workgroup decodes a 128-row x 128-column weight tile at a time into
  * LDS (every vector A q + B in fp32 from the exact integer codes, rounded

@@ -172,7 +172,7 @@ def test_gemm_workspace():
     assert ws(16, 128, 0, u.BF16) == 0
     assert ws(16, 128, 1, u.F32) == 0
     # up to 16 tokens the small-batch kernel needs nothing; from 17 to 32 the
-    # size also covers the tiled product (the launch's width picks the kernel);
+    # size also covers the tiled product (the launch's shape picks the kernel);
     # a product with few output tiles is split along K: fp32 partials for every split
     assert ws(64, 1024, 16, u.F16) == 0
     for m in (17, 32, 33):
@@ -545,7 +545,7 @@ def test_gemm_batched_validation():
     assert f(bad, 2, 16, u.F16, u.F16, None, 0, None) == ESHAPE
     mis = (P * 2)(P(4096, 4096, GOOD, GOOD, GOOD), P(1024, 4096, GOOD, GOOD + 8, GOOD))
     assert f(mis, 2, 16, u.F16, u.F16, None, 0, None) == EALIGN
-    # fp16 activations at <= 32 tokens need no workspace; bf16 needs one slice per problem
+    # fp16 activations at <= 16 tokens need no workspace; bf16 needs one slice per problem
     assert lib.unisvq_gemm_batched_workspace_bytes(two, 2, 16, u.F16) == 0
     need = lib.unisvq_gemm_batched_workspace_bytes(two, 2, 16, u.BF16)
     singles = [lib.unisvq_gemm_workspace_bytes(N, 4096, 16, u.BF16) for N in (4096, 1024)]

@@ -398,9 +398,10 @@ def test_graph_replays_cover_every_launch_family():
     """Every other launch family captured in one HIP graph, with eager work
     (fills and launches of the same kernels on other inputs) between the
     replays; each replay reproduces the eager results bit for bit: batched
-    small-batch launches (16 tokens, workgroups across problems; 24 tokens,
-    two token tiles), a wide 24-token batch (tiled, K split and reduction),
-    bf16 activations (row-major and tiled pre-passes), row-shared pairs with the Eq. 9 fold (its pre-pass),
+    small-batch launches (16 tokens, workgroups across problems), the kernel of
+    17 to 64 tokens (24 tokens, a narrow and a wide batch; 64 tokens, f16
+    activations copied to tiles), a 100-token batch (tiled, K split and
+    reduction), bf16 activations (row-major and tiled pre-passes), row-shared pairs with the Eq. 9 fold (its pre-pass),
     the input transform fused into the matrix-vector product, standalone
     transforms (fast Walsh-Hadamard and Paley orders) and a 3-bit d = 8
     variant product."""
@@ -409,12 +410,14 @@ def test_graph_replays_cover_every_launch_family():
     for i in range(3):
         Q, A, B = wl.gen_weights(1024, K, seed=150 + i)
         probs.append(upload_pack(Q, A, B))
-    wide = []  # 3 x 4096 rows: 96 tiles of 128, the tiled product at 24 tokens
+    wide = []  # 3 x 4096 rows: four row blocks per workgroup at 24 tokens
     for i in range(3):
         Q, A, B = wl.gen_weights(4096, K, seed=170 + i)
         wide.append(upload_pack(Q, A, B))
     x16 = dev_x(wl.gen_activations(16, K, seed=151, outliers=True), "f16")
     x24 = dev_x(wl.gen_activations(24, K, seed=152), "f16")
+    x64 = dev_x(wl.gen_activations(64, K, seed=161), "f16")
+    x100 = dev_x(wl.gen_activations(100, K, seed=162), "f16")
     xb16 = dev_x(wl.gen_activations(16, K, seed=153, dtype="bf16"), "bf16")
     xb64 = dev_x(wl.gen_activations(64, K, seed=154, dtype="bf16"), "bf16")
     Qs, As, Bs = wl.gen_shared_weights(1024, K, 1, seed=155)
@@ -435,6 +438,9 @@ def test_graph_replays_cover_every_launch_family():
                                   out_dtype=torch.float32)
         r["w24"] = u.gemm_batched([(pk, 4096, K, x24, o.get("w24", [None] * 3)[i]) for i, pk in enumerate(wide)],
                                   out_dtype=torch.float32)
+        r["c64"] = u.gemm_batched([(pk, 4096, K, x64, o.get("c64", [None] * 3)[i]) for i, pk in enumerate(wide)])
+        r["t100"] = u.gemm_batched([(pk, 1024, K, x100, o.get("t100", [None] * 3)[i]) for i, pk in enumerate(probs)],
+                                   out_dtype=torch.float32)
         r["bf16"] = [u.gemm(probs[0], 1024, K, xb16, out=o.get("bf16", [None])[0], out_dtype=torch.float32)]
         r["bf64"] = [u.gemm(probs[1], 1024, K, xb64, out=o.get("bf64", [None])[0], out_dtype=torch.float32)]
         r["fold"] = [u.gemm_shared_fold(pc, pa, 1024, K, 1, xb64, out=o.get("fold", [None])[0],

@@ -43,11 +43,12 @@ def call_noalloc(u, pk, N, K, x, y):
 
 
 # (first call, second smaller call): bf16 activations use the scratch for the
-# fp16 copy (tiled above 32 tokens) and, at few tokens, the K-split partials;
-# fp16 activations at 80 tokens only for the partials
+# fp16 copy (tiled above 16 tokens) and, at few tokens, the K-split partials;
+# fp16 activations at 80 tokens for the partials, at 48 and 40 for their tiled copy
 @pytest.mark.parametrize("dtype,first,second", [
     ("bf16", (4096, 4096, 300), (1024, 4096, 70)),
     ("f16", (4096, 11008, 80), (2048, 4096, 70)),
+    ("f16", (4096, 11008, 48), (2048, 4096, 40)),
     ("bf16", (11008, 4096, 64), (4096, 4096, 16)),
 ])
 def test_noalloc_equals_workspace_path(lib, dtype, first, second):
